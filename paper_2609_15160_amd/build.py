@@ -11,7 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtlf.so")
-SOURCES = ["api.hip", "gemm.hip", "dgemm.hip", "plan.hip", "attn.hip", "rows.hip", "cond.hip", "gs.hip",
+SOURCES = ["api.hip", "gemm.hip", "pgemm.hip", "dgemm.hip", "plan.hip", "attn.hip", "rows.hip", "cond.hip", "gs.hip",
            "noalloc.hip", "probe.hip"]
 
 HIPCC_FLAGS = [

@@ -20,8 +20,8 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 enum Buf {
   B_POOL, B_POS, B_PAGE_TABLE, B_CACHE_LEN, B_CHUNK_LEN, B_SEQ_LEN, B_SCALARS, B_DEPTH_HIST, B_STEP_STATS,
   B_X_DEC, B_XC_DEC, B_KVSLOT, B_DEPTH_DEC, B_PERM, B_NACT, B_Q_DEC, B_O_DEC, B_ACT_DEC, B_KEYS,
-  B_X_PRE, B_Y_PRE, B_Y16_PRE, B_DEPTH_PRE, B_TOK_IDX, B_KVSLOT_PRE, B_Q_PRE, B_O_PRE, B_ACT_PRE, B_HID,
-  B_ROW_DEPTH, B_MOD, B_COND_TMP, B_WFRAG, B_TILES,
+  B_X_PRE, B_Y_PRE, B_DEPTH_PRE, B_TOK_IDX, B_KVSLOT_PRE, B_Q_PRE, B_O_PRE, B_ACT_PRE, B_HID,
+  B_ROW_DEPTH, B_MOD, B_COND_TMP, B_WFRAG, B_PRE_NACT, B_PRE_CNT, B_PRE_OFF,
   B_COUNT
 };
 
@@ -62,10 +62,7 @@ bool make_layout(const tlf_config& c, Layout* L) {
   sz[B_ACT_DEC] = (int64_t)((B + 15) / 16 * 16) * F * 4;  // whole groups of 16 rows (fragment order)
   sz[B_KEYS] = B * ceil_div(c.vocab, kWave) * 8;  // greedy key per 64-column group of each row
   sz[B_X_PRE] = P * d * 4;
-  sz[B_Y_PRE] = P * d * 4;
-  // one-part bf16 prefill activations: RMSNorm(x) as bf16 rows (o and act
-  // are written as bf16 into their own float buffers)
-  sz[B_Y16_PRE] = c.prefill_act_bf16 && c.dtype == TLF_DTYPE_BF16 ? P * d * 2 : 0;
+  sz[B_Y_PRE] = P * d * 4;  // float32 rows, or (bf16 models) operand rows of one or two bf16 parts
   sz[B_DEPTH_PRE] = P * 4;
   sz[B_TOK_IDX] = R * P * 4;
   sz[B_KVSLOT_PRE] = R * P * 8;
@@ -79,8 +76,11 @@ bool make_layout(const tlf_config& c, Layout* L) {
   sz[B_COND_TMP] = c.adaln ? (int64_t)cond_scratch_floats((int)R, (int)d) * 4 : 0;
   // every layer's block weights in MFMA fragment order (the decode projections' copy)
   sz[B_WFRAG] = (int64_t)c.n_layers * (4 * d * d + 3 * d * F) * s;
-  // each prefill loop's active row-tile counts and lists (one-part bf16 activations)
-  sz[B_TILES] = c.prefill_act_bf16 && c.dtype == TLF_DTYPE_BF16 ? R * (3 + P / 64 + P / 128 + P / 256) * 4 : 0;
+  // prefill planner: gathered rows of each loop, and per sequence of the group
+  // (a group has at most max_batch) its count and first row per loop
+  sz[B_PRE_NACT] = R * 4;
+  sz[B_PRE_CNT] = B * R * 4;
+  sz[B_PRE_OFF] = B * R * 4;
   size_t off = 0;
   for (int i = 0; i < B_COUNT; ++i) {
     if (sz[i] < 0) return false;
@@ -295,7 +295,7 @@ constexpr int kHeadGemmRows = 128;
 
 // Prefill of a single sequence of at most this many tokens runs its
 // projections on the split-K decode GEMM.
-constexpr int kPrefillFewRows = 2048;
+constexpr int kPrefillFewRows = 64;
 
 // AdaLN: point a projection at its rows' modulation at (loop i, layer j):
 // part 0..3 = alpha_msa, alpha_mlp, gamma_msa, gamma_mlp of the table
@@ -333,26 +333,22 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
   for (int b0 = 0; b0 < B; b0 += G) {
     const int Gc = std::min(G, B - b0);
     const int rows = Gc * T_;
-    // one short sequence: too few rows for the 128 x 128 tiles to fill the
-    // device, so the projections take the split-K decode GEMM with the
-    // RMSNorm fused (x is read through the gathered positions, no y)
+    // one short sequence: the projections take the split-K decode GEMM with
+    // the RMSNorm fused (x is read through the gathered positions, no y)
     const bool few = Gc == 1 && T_ <= kPrefillFewRows;
-    // one-part bf16 activations (prefill_act_bf16, bf16 weights, the many-row
-    // GEMMs): RMSNorm(x), o and act are handed on as bf16 rows; the LM head
-    // keeps reading the float32 RMSNorm(x)
-    const bool one = c.prefill_act_bf16 && c.dtype == TLF_DTYPE_BF16 && !few;
-    // with the normed rows handed on as bf16 and no AdaLN scale to apply to
-    // the float rows, RMSNorm(x) in float32 feeds only the LM head: it is
-    // written once, for the head's rows, after the last loop
-    const bool y32 = !one || c.adaln;
-    bf16* y16 = one ? ctx->buf<bf16>(B_Y16_PRE) : nullptr;
-    bf16* o16 = one ? ctx->buf<bf16>(B_O_PRE) : nullptr;
-    bf16* act16 = one ? ctx->buf<bf16>(B_ACT_PRE) : nullptr;
+    // bf16 models: RMSNorm(x), o and act are handed on as bf16 operand rows of
+    // two parts, or of one (prefill_act_bf16); the LM head always takes two
+    const bool parted = c.dtype == TLF_DTYPE_BF16 && !few;
+    const int parts = c.prefill_act_bf16 ? 1 : 2;
+    bf16* y16 = parted ? ctx->buf<bf16>(B_Y_PRE) : nullptr;
+    bf16* o16 = parted ? ctx->buf<bf16>(B_O_PRE) : nullptr;
+    bf16* act16 = parted ? ctx->buf<bf16>(B_ACT_PRE) : nullptr;
     EmbedArgs ea;
     ea.tok_emb = ctx->w.tok_emb; ea.pos_emb = ctx->w.pos_emb; ea.Wr = ctx->w.router_w; ea.br = ctx->w.router_b;
     ea.tokens = tokens + (int64_t)b0 * T_;
     ea.rows = rows; ea.V = c.vocab; ea.d = d; ea.R = R; ea.prefill_T = T_; ea.pos0 = pos0;
-    ea.x = x; ea.y = few || !y32 ? nullptr : y; ea.y16 = y16; ea.eps = c.rms_eps; ea.depth = ctx->buf<int32_t>(B_DEPTH_PRE);
+    ea.x = x; ea.y = few || parted ? nullptr : y; ea.y16 = c.adaln ? nullptr : y16; ea.parts = parts; ea.eps = c.rms_eps;
+    ea.depth = ctx->buf<int32_t>(B_DEPTH_PRE);
     ea.out_depth = depths ? depths + (int64_t)b0 * T_ : nullptr;
     ea.rule = c.route_rule; ea.threshold = c.route_threshold; ea.fixed = c.fixed_depth;
     ea.err = ctx->cv.err;
@@ -368,99 +364,91 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     pa.depth = ctx->buf<int32_t>(B_DEPTH_PRE);
     pa.tok_idx = ctx->buf<int32_t>(B_TOK_IDX);
     pa.kv_slot = ctx->buf<int64_t>(B_KVSLOT_PRE);
-    // the later loops' projections take smaller tiles from each loop's list
-    // of active row tiles (whole tiles per sequence: T a multiple of 256)
-    const bool tiles = one && T_ % 256 == 0 && ctx->L.size[B_TILES] > 0;
-    int32_t* tile_cnt = ctx->buf<int32_t>(B_TILES);
-    int32_t* tile_list64 = tile_cnt + 3 * R;
-    int32_t* tile_list128 = tile_list64 + (int64_t)R * (ctx->L.pre_rows / 64);
-    int32_t* tile_list256 = tile_list128 + (int64_t)R * (ctx->L.pre_rows / 128);
-    if (tiles) {
-      TLF_HIP(launch_fill_i32(tile_cnt, 0, 3 * R, s));
-      pa.tile_cnt = tile_cnt; pa.tile_list64 = tile_list64; pa.tile_list128 = tile_list128;
-      pa.tile_list256 = tile_list256;
-    }
+    pa.nact = ctx->buf<int32_t>(B_PRE_NACT); pa.seq_cnt = ctx->buf<int32_t>(B_PRE_CNT);
+    pa.row_off = ctx->buf<int32_t>(B_PRE_OFF);
     TLF_HIP(launch_plan_prefill(pa, s));
 
+    // RMSNorm(x) after a residual projection, for the projection at (loop ni,
+    // layer nj) that reads it next: with operand rows its AdaLN scale (table
+    // part 2 QKV, 3 gate/up) is applied here
+    ResidNormArgs rn;
+    rn.x = x; rn.y = parted ? nullptr : y; rn.y16 = y16; rn.parts = parts; rn.d = d; rn.eps = c.rms_eps;
+    auto norm = [&](const RowMap& rm, int ni, int nj, int part) {
+      rn.rm = rm;
+      rn.mod_g = nullptr;
+      if (parted && c.adaln && ni < R) {
+        GemmArgs m;
+        set_mod(ctx, &m, ni, nj, part, pre_depth, 1);
+        rn.mod_g = m.mod_g; rn.mod_ld = m.mod_ld; rn.mod_depth = m.mod_depth;
+      }
+      return launch_resid_norm<T>(rn, s);
+    };
+    if (parted && c.adaln) {  // the scale needs the depths, so the embedding wrote no y
+      RowMap all;
+      all.rows = rows;
+      TLF_HIP(norm(all, 0, 0, 2));
+    }
+    auto project = [&](const GemmArgs& g, AKind ak, EKind ek) {
+      if (few) return launch_dgemm<T>(g, ak, ek, ek == E_QKV || ek == E_SWIGLU, ctx->cus, s);
+      if (parted) return launch_pgemm(g, ak, ek, parts, ctx->cus, s);
+      return launch_gemm<T>(g, ak, ek, false, s);
+    };
+
     for (int i = 0; i < R; ++i) {
-      // rows: G segments of T compact slots; slot a of segment g is the a-th
-      // token of the call in sequence b0 + g with depth >= i + 1 (cache
-      // entry n_old + a), residual row tok_idx[r]
+      // row r < n_i is the r-th gathered token of loop i, residual row tok_idx[r]
       RowMap rm;
       rm.src = ctx->buf<int32_t>(B_TOK_IDX) + (int64_t)i * rows;
-      rm.seg_cnt = ctx->cv.chunk_len + (int64_t)b0 * R + i;
-      rm.seg = T_; rm.seg_cnt_stride = R; rm.rows = rows;
-      if (few) rm.nact = rm.seg_cnt;  // one segment: rows [0, n) active
-      TileList tl;
-      if (tiles) {
-        tl.cnt = tile_cnt + 3 * i;
-        tl.list64 = tile_list64 + (int64_t)i * (rows / 64);
-        tl.list128 = tile_list128 + (int64_t)i * (rows / 128);
-        tl.list256 = tile_list256 + (int64_t)i * (rows / 256);
-        tl.cus = ctx->cus;
-      }
-      ResidNormArgs rn;
-      rn.rm = rm; rn.x = x; rn.y = y32 ? y : nullptr; rn.y16 = y16; rn.d = d; rn.eps = c.rms_eps;
+      rm.nact = pa.nact + i;
+      rm.rows = rows;
       for (int j = 0; j < c.n_layers; ++j) {
         const tlf_layer_weights& lw = ctx->layers[j];
         GemmArgs q;
         q.A = few ? x : y; q.lda = d; q.W = lw.w_qkv; q.Wf = ctx->wfrag(j, 0); q.N = 3 * d; q.K = d; q.w_rows = 3 * d; q.rm = rm;
         q.out = ctx->buf<float>(B_Q_PRE); q.ldo = d; q.d = d; q.eps = c.rms_eps; q.spec = i == 0;
         q.kv.c = ctx->cv; q.kv.loop = i; q.kv.layer = j; q.kv.slot_base = ctx->buf<int64_t>(B_KVSLOT_PRE) + (int64_t)i * rows;
-        set_mod(ctx, &q, i, j, 2, pre_depth, 1);
-        q.a_single = one;
-        if (one && !q.mod_g) q.A16 = y16;  // the AdaLN scale needs the float rows
+        if (parted) q.A16 = y16;
+        else set_mod(ctx, &q, i, j, 2, pre_depth, 1);
         const float scale_log2 = 1.4426950408889634f / std::sqrt((float)c.head_dim);
         // one part: q handed on as bf16(q * scale_log2), as the attention rounds it
-        bf16* q16 = one ? reinterpret_cast<bf16*>(ctx->buf<float>(B_Q_PRE)) : nullptr;
-        q.q16 = q16; q.q_scale = scale_log2; q.tl = tl;
-        if (few) TLF_HIP(launch_dgemm<T>(q, A_SRC, E_QKV, true, ctx->cus, s));
-        else TLF_HIP(launch_gemm<T>(q, A_SRC, E_QKV, false, s));
+        bf16* q16 = parted && parts == 1 ? reinterpret_cast<bf16*>(ctx->buf<float>(B_Q_PRE)) : nullptr;
+        q.q16 = q16; q.q_scale = scale_log2;
+        TLF_HIP(project(q, A_SRC, E_QKV));
 
         AttnPrefillArgs at;
         at.c = ctx->cv; at.loop = i; at.layer = j; at.d = d; at.b0 = b0; at.G = Gc; at.T = T_;
+        at.row_off = pa.row_off;
         at.q = ctx->buf<float>(B_Q_PRE); at.o = ctx->buf<float>(B_O_PRE);
         at.scale_log2 = scale_log2;
-        at.q_single = one;
         at.q16 = q16;
-        at.o16 = o16;
+        at.o16 = o16; at.o_parts = parts;
         TLF_HIP(launch_attn_prefill<T>(at, s));
 
         GemmArgs o;
         o.A = ctx->buf<float>(B_O_PRE); o.lda = d; o.W = lw.w_o; o.Wf = ctx->wfrag(j, 1); o.N = d; o.K = d; o.w_rows = d; o.rm = rm;
-        o.out = x; o.ldo = d; o.scatter = 1; o.spec = i == 0; o.a_single = one; o.A16 = o16; o.tl = tl;
+        o.out = x; o.ldo = d; o.scatter = 1; o.spec = i == 0; o.A16 = o16;
         set_mod(ctx, &o, i, j, 0, pre_depth, 1);
-        if (few) {
-          TLF_HIP(launch_dgemm<T>(o, A_CMP, E_RESID, false, ctx->cus, s));
-        } else {
-          TLF_HIP(launch_gemm<T>(o, A_CMP, E_RESID, false, s));
-          TLF_HIP(launch_resid_norm<T>(rn, s));
-        }
+        TLF_HIP(project(o, A_CMP, E_RESID));
+        if (!few) TLF_HIP(norm(rm, i, j, 3));
 
         GemmArgs gu;
         gu.A = few ? x : y; gu.lda = d; gu.W = lw.w_gate_up; gu.Wf = ctx->wfrag(j, 2); gu.N = 2 * F; gu.K = d; gu.w_rows = 2 * F; gu.rm = rm;
         gu.out = ctx->buf<float>(B_ACT_PRE); gu.ldo = F; gu.F = F; gu.eps = c.rms_eps; gu.spec = i == 0;
-        gu.a_single = one; gu.out16 = act16; gu.tl = tl;
-        set_mod(ctx, &gu, i, j, 3, pre_depth, 1);
-        if (one && !gu.mod_g) gu.A16 = y16;
-        if (few) TLF_HIP(launch_dgemm<T>(gu, A_SRC, E_SWIGLU, true, ctx->cus, s));
-        else TLF_HIP(launch_gemm<T>(gu, A_SRC, E_SWIGLU, false, s));
+        gu.out16 = act16;
+        if (parted) gu.A16 = y16;
+        else set_mod(ctx, &gu, i, j, 3, pre_depth, 1);
+        TLF_HIP(project(gu, A_SRC, E_SWIGLU));
 
         GemmArgs dn;
         dn.A = ctx->buf<float>(B_ACT_PRE); dn.lda = F; dn.W = lw.w_down; dn.Wf = ctx->wfrag(j, 3); dn.N = d; dn.K = F; dn.w_rows = d;
-        dn.rm = rm; dn.out = x; dn.ldo = d; dn.scatter = 1; dn.spec = i == 0; dn.a_single = one; dn.A16 = act16;
-        dn.tl = tl;
+        dn.rm = rm; dn.out = x; dn.ldo = d; dn.scatter = 1; dn.spec = i == 0; dn.A16 = act16;
         set_mod(ctx, &dn, i, j, 1, pre_depth, 1);
-        if (few) {
-          TLF_HIP(launch_dgemm<T>(dn, A_CMP, E_RESID, false, ctx->cus, s));
-        } else {
-          TLF_HIP(launch_gemm<T>(dn, A_CMP, E_RESID, false, s));
-          TLF_HIP(launch_resid_norm<T>(rn, s));
-        }
+        TLF_HIP(project(dn, A_CMP, E_RESID));
+        const bool last = j + 1 == c.n_layers;
+        if (!few) TLF_HIP(norm(rm, last ? i + 1 : i, last ? 0 : j + 1, 2));
       }
     }
     GemmArgs hd;
-    hd.A = few ? x : y; hd.lda = d; hd.W = head_weights(ctx); hd.N = c.vocab; hd.K = d; hd.w_rows = c.vocab;
+    hd.A = x; hd.lda = d; hd.W = head_weights(ctx); hd.N = c.vocab; hd.K = d; hd.w_rows = c.vocab;
     hd.out = logits; hd.ldo = c.vocab; hd.eps = c.rms_eps; hd.spec = 1;
     if (flags & TLF_PREFILL_ALL_LOGITS) {
       hd.rm.rows = rows; hd.rm.src_stride = 1; hd.rm.src_off = 0;
@@ -469,13 +457,19 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
       hd.rm.rows = Gc; hd.rm.src_stride = T_; hd.rm.src_off = T_ - 1;
       hd.out_row_off = b0;
     }
-    if (!y32) {
-      ResidNormArgs hn;
-      hn.rm = hd.rm; hn.x = x; hn.y = y; hn.d = d; hn.eps = c.rms_eps;
-      TLF_HIP(launch_resid_norm<T>(hn, s));
+    if (hd.rm.rows < kHeadGemmRows) {  // few rows: the norm fused
+      TLF_HIP(launch_dgemm<T>(hd, A_SRC, E_LOGITS, true, ctx->cus, s));
+    } else if (parted) {
+      if (parts == 1 || c.adaln) {  // y16 holds one part, or the last projection's scale
+        rn.parts = 2;
+        TLF_HIP(norm(hd.rm, R, 0, 2));
+      }
+      hd.A16 = y16;
+      TLF_HIP(launch_pgemm(hd, A_SRC, E_LOGITS, 2, ctx->cus, s));
+    } else {
+      hd.A = y;
+      TLF_HIP(launch_gemm<T>(hd, A_SRC, E_LOGITS, false, s));
     }
-    if (few) TLF_HIP(launch_dgemm<T>(hd, A_SRC, E_LOGITS, true, ctx->cus, s));
-    else TLF_HIP(launch_gemm<T>(hd, A_SRC, E_LOGITS, false, s));
   }
   return TLF_OK;
 }

@@ -19,7 +19,7 @@
 // S^T = K q^T, so that the P^T operand of O^T = V^T P^T is exactly the scores
 // each lane holds (no data movement between the two products); both run on
 // MFMA with an online softmax per query.  Against bf16 keys q enters as hi +
-// lo parts, or as one bf16 part when the caller asks for it (q_single).
+// lo parts, or as the one bf16 part that the projection wrote (q16).
 #include "kernels.h"
 
 namespace tlf {
@@ -370,6 +370,7 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
   const int n0 = n - nq;
   const int q0 = qt * BQ;
   if (q0 >= nq) return;
+  const int row0 = a.row_off[g * c.R + a.loop];  // compact row of the sequence's first query
   const int32_t* pt = c.page_table + ((int64_t)b * c.R + a.loop) * c.pages_per_seq;
   const T* pool = reinterpret_cast<const T*>(c.pool);
   const int64_t koff = k_block(c, a.layer, h), voff = v_block(c, a.layer, h);
@@ -384,7 +385,8 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
 #pragma unroll
   for (int qn = 0; qn < QN; ++qn) {
     const int qrow = min(q0 + w * QW + qn * 16 + c16, nq - 1);
-    const float* qp = a.q + ((int64_t)g * a.T + qrow) * a.d + h * D + quad * EPL;
+    const int64_t qo = (int64_t)(row0 + qrow) * a.d + h * D + quad * EPL;
+    const float* qp = a.q + qo;
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
       if constexpr (NQ == 2) {
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
         qf[qn][1][ks] = __builtin_bit_cast(Frag, make_uint4(l0.x, l0.y, l1.x, l1.y));
       } else if constexpr (EPL == 8) {
         if (a.q16) {  // written scaled and rounded by the QKV projection
-          qf[qn][0][ks] = *reinterpret_cast<const Frag*>(a.q16 + (qp - a.q) + ks * KS);
+          qf[qn][0][ks] = *reinterpret_cast<const Frag*>(a.q16 + qo + ks * KS);
         } else {
           const float4 v0 = scale4(*reinterpret_cast<const float4*>(qp + ks * KS), a.scale_log2);
           const float4 v1 = scale4(*reinterpret_cast<const float4*>(qp + ks * KS + 4), a.scale_log2);
@@ -642,19 +644,15 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
     lt = sum_xor32(sum_xor16(lt));
     const int row = q0 + w * QW + qn * 16 + c16;
     if (row >= nq) continue;
-    const int64_t oo = ((int64_t)g * a.T + row) * a.d + h * D + 4 * quad;
+    const int64_t orow = row0 + row;
     const float inv = 1.f / lt;
-    if (a.o16) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        *reinterpret_cast<uint2*>(a.o16 + oo + dt * 16) =
-            make_uint2(pack_bf16x2(o[dt][qn][0] * inv, o[dt][qn][1] * inv),
-                       pack_bf16x2(o[dt][qn][2] * inv, o[dt][qn][3] * inv));
-    } else {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        *reinterpret_cast<float4*>(a.o + oo + dt * 16) =
-            make_float4(o[dt][qn][0] * inv, o[dt][qn][1] * inv, o[dt][qn][2] * inv, o[dt][qn][3] * inv);
+    for (int dt = 0; dt < DT; ++dt) {
+      const float4 v = make_float4(o[dt][qn][0] * inv, o[dt][qn][1] * inv, o[dt][qn][2] * inv, o[dt][qn][3] * inv);
+      const int k = h * D + 4 * quad + dt * 16;
+      if (!a.o16) *reinterpret_cast<float4*>(a.o + orow * a.d + k) = v;
+      else if (a.o_parts == 2) store_operand4<2>(a.o16, orow, k, a.d, v);
+      else store_operand4<1>(a.o16, orow, k, a.d, v);
     }
   }
 }
@@ -721,11 +719,11 @@ hipError_t launch_attn_prefill(const AttnPrefillArgs& a, hipStream_t s) {
         return hipErrorInvalidValue;
       }
     case 64:
-      if (sizeof(T) == 2 && a.q_single) hipLaunchKernelGGL((k_attn_prefill<T, 64, false>), grid, block, 0, s, a);
+      if (sizeof(T) == 2 && a.q16) hipLaunchKernelGGL((k_attn_prefill<T, 64, false>), grid, block, 0, s, a);
       else hipLaunchKernelGGL((k_attn_prefill<T, 64, true>), grid, block, 0, s, a);
       break;
     case 128:
-      if (sizeof(T) == 2 && a.q_single) hipLaunchKernelGGL((k_attn_prefill<T, 128, false>), grid, block, 0, s, a);
+      if (sizeof(T) == 2 && a.q16) hipLaunchKernelGGL((k_attn_prefill<T, 128, false>), grid, block, 0, s, a);
       else hipLaunchKernelGGL((k_attn_prefill<T, 128, true>), grid, block, 0, s, a);
       break;
     default: return hipErrorInvalidValue;

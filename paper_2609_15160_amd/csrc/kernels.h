@@ -9,24 +9,20 @@ namespace tlf {
 // Row maps: which GEMM rows are active and where their residual row lives.
 //   decode : row k < n_i is the k-th deepest token of the step, residual row
 //            perm[k]; rows >= n_i have exited (Section 3.3 early exit).
-//   prefill: rows are G segments of T compact slots; slot a of segment g is
-//            active while a < n_{g,i}, and its residual row is tok_idx[r]
-//            (the gathered original position, Eq. 6).
+//   prefill: row r < n_i is the r-th gathered token of loop i (sequence by
+//            sequence, in position order), residual row tok_idx[r] (Eq. 6).
 //   plain  : rows [0, rows) active, residual row r * src_stride + src_off.
 // ---------------------------------------------------------------------------
 struct RowMap {
   const int32_t* src = nullptr;   // residual row of row r (nullptr: strided)
   int src_stride = 1, src_off = 0;
-  const int32_t* nact = nullptr;  // decode: rows [0, *nact) are active
-  const int32_t* seg_cnt = nullptr; // prefill: segment s has seg_cnt[s * seg_cnt_stride] active slots
-  int seg = 0, seg_cnt_stride = 0;
+  const int32_t* nact = nullptr;  // rows [0, *nact) are active
   int rows = 0;                   // rows covered by the grid
 };
 
 __device__ __forceinline__ bool row_active(const RowMap& m, int r) {
   if (r >= m.rows) return false;
   if (m.nact) return r < *m.nact;
-  if (m.seg_cnt) return (r % m.seg) < m.seg_cnt[(r / m.seg) * m.seg_cnt_stride];
   return true;
 }
 __device__ __forceinline__ int row_src(const RowMap& m, int r) {
@@ -55,18 +51,6 @@ enum AKind { A_SRC = 0, A_CMP = 1 };
 // E_LOGITS: float logits + greedy keys.  E_HIDDEN: out[r] = silu(result + bias)
 // (the MLP router's hidden layer).
 enum EKind { E_QKV = 0, E_RESID = 1, E_SWIGLU = 3, E_LOGITS = 4, E_HIDDEN = 5 };
-
-// Active row tiles of a prefill loop, listed by the planner (sequences of a
-// multiple of 256 tokens): with few of them the many-row GEMM takes smaller
-// tiles from the list, so that more workgroups share the K loops of the
-// later loops.
-struct TileList {
-  const int32_t* cnt = nullptr;      // this loop's active row tiles: [0] of 64 rows, [1] of 128, [2] of 256
-  const int32_t* list64 = nullptr;   // first rows of the active 64-row tiles (inside one segment)
-  const int32_t* list128 = nullptr;  // first rows of the active 128-row tiles
-  const int32_t* list256 = nullptr;  // first rows of the active 256-row tiles
-  int cus = 0;                       // compute units
-};
 
 struct GemmArgs {
   const float* A = nullptr; // float32 rows
@@ -110,13 +94,10 @@ struct GemmArgs {
   int mod_by_src = 0;
   const int32_t* keep_depth = nullptr;  // E_RESID (dense decode): row r is stored only while
   int keep_loop = 0;                    // keep_depth[r] > keep_loop (its token runs this loop)
-  int a_single = 0;         // launch_gemm with bf16 weights: A rounded to one bf16 part (not hi + lo)
-  const bf16* A16 = nullptr;  // launch_gemm with bf16 weights: A given as bf16 rows (same lda) in place of
-                              // A (no norm, no operand modulation)
-  bf16* out16 = nullptr;      // launch_gemm E_SWIGLU: act rows written as bf16 instead of float
-  bf16* q16 = nullptr;        // launch_gemm E_QKV: q rows written as bf16(q * q_scale) instead of to out
+  const bf16* A16 = nullptr;  // launch_pgemm: the operand rows in one or two bf16 parts (operand_off)
+  bf16* out16 = nullptr;      // launch_pgemm E_SWIGLU: act as operand rows of the same number of parts
+  bf16* q16 = nullptr;        // launch_pgemm E_QKV, one part: q rows written as bf16(q * q_scale) instead of to out
   float q_scale = 1.f;
-  TileList tl;                // launch_gemm with A16: the loop's active tiles (tl.cnt set) for the small shape
 };
 
 // Offset of element (R, k) of a [rows][K] operand stored in MFMA fragment order.
@@ -125,10 +106,34 @@ template <typename T> __device__ __forceinline__ int64_t frag_index(int R, int k
   return ((int64_t)((R >> 4) * (K / KS) + k / KS) * kWave + (k % KS) / EPL * 16 + (R & 15)) * EPL + k % EPL;
 }
 
-// Many-row projections (prefill, and the decode LM head of a large batch):
-// 128 x 128 MFMA tiles staged through LDS.  norm: A is the residual x and the
-// product is taken with RMSNorm(x) (supported for (A_CMP, E_LOGITS), whose
-// rows write their logits to row src(r)).
+// Prefill activations as bf16 operand rows: one part, [row][K], or hi and lo
+// parts side by side, [row][K / 32][hi 32 | lo 32], hi = bf16(v),
+// lo = bf16(v - hi).  Offset of (the hi part of) element (row, k); the lo part
+// lies 32 elements on.
+template <int P> __device__ __forceinline__ int64_t operand_off(int64_t row, int k, int K) {
+  return P == 2 ? row * (2 * K) + (k >> 5) * 64 + (k & 31) : row * K + k;
+}
+// Four consecutive elements, k a multiple of 4.
+template <int P> __device__ __forceinline__ void store_operand4(bf16* p, int64_t row, int k, int K, float4 v) {
+  bf16* o = p + operand_off<P>(row, k, K);
+  if constexpr (P == 2) {
+    uint2 hi, lo;
+    split4(v, hi, lo);
+    *reinterpret_cast<uint2*>(o) = hi;
+    *reinterpret_cast<uint2*>(o + 32) = lo;
+  } else {
+    *reinterpret_cast<uint2*>(o) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+  }
+}
+
+// Prefill projections of bf16 models (pgemm.hip): A as bf16 operand rows of
+// `parts` parts, weights in fragment order (the LM head's row-major).
+// Supported: (A_SRC, E_QKV | E_SWIGLU | E_LOGITS), (A_CMP, E_RESID).
+hipError_t launch_pgemm(const GemmArgs& a, AKind ak, EKind ek, int parts, int cus, hipStream_t s);
+// Many-row projections of float32 models, the MLP router's hidden layer and
+// the decode LM head of a large batch: MFMA tiles staged through LDS.  norm:
+// A is the residual x and the product is taken with RMSNorm(x) (supported for
+// (A_CMP, E_LOGITS), whose rows write their logits to row src(r)).
 template <typename T>
 hipError_t launch_gemm(const GemmArgs& a, AKind ak, EKind ek, bool norm, hipStream_t s);
 // Decode-shaped projections (few rows): K split across the waves of a
@@ -170,7 +175,8 @@ struct EmbedArgs {
   const int32_t* seq_len = nullptr;
   float* x = nullptr;             // [rows][d] float residual
   float* y = nullptr;             // [rows][d] RMSNorm(x), or nullptr
-  bf16* y16 = nullptr;            // [rows][d] RMSNorm(x) rounded to bf16, or nullptr
+  bf16* y16 = nullptr;            // RMSNorm(x) as operand rows of `parts` bf16 parts, or nullptr
+  int parts = 1;
   float eps = 1e-5f;
   int32_t* depth = nullptr;       // [rows]
   int32_t* out_depth = nullptr;   // optional [rows]
@@ -202,9 +208,15 @@ struct ResidNormArgs {
   RowMap rm;
   const float* x = nullptr;
   float* y = nullptr;       // or nullptr
-  bf16* y16 = nullptr;      // also RMSNorm(x) rounded to bf16, or nullptr
+  bf16* y16 = nullptr;      // RMSNorm(x) (1 + gamma) as operand rows of `parts` bf16 parts, or nullptr
+  int parts = 1;
   int d = 0;
   float eps = 1e-5f;
+  // AdaLN scale of the projection that reads y16 (nullptr: none): row r's
+  // gamma sits at (depth[src(r)] - 1) * mod_ld
+  const float* mod_g = nullptr;
+  int mod_ld = 0;
+  const int32_t* mod_depth = nullptr;
 };
 template <typename T> hipError_t launch_resid_norm(const ResidNormArgs& a, hipStream_t s);
 
@@ -227,22 +239,20 @@ struct DecodePlanArgs {
 };
 hipError_t launch_plan_decode(const DecodePlanArgs& a, hipStream_t s);
 
-// Prefill planner (one workgroup per sequence of the group): per loop i the
-// gathered positions rho^(i) (Eq. 6), n_{b,i}, pages and their positions.
+// Prefill planner: per loop i the gathered tokens rho^(i) of every sequence
+// of the group (Eq. 6), packed sequence by sequence, n_{b,i}, pages and their
+// positions.
 struct PrefillPlanArgs {
   CacheView c;
   int b0 = 0, G = 0, T = 0;
   int append = 0;  // 1: continue every (b, i) cache after its cache_len entries; 0: start it empty
   int pos0 = 0;    // position of the first token of the call
   const int32_t* depth = nullptr;  // [G][T]
-  int32_t* tok_idx = nullptr;      // [R][G*T]
+  int32_t* tok_idx = nullptr;      // [R][G*T]: the loop's gathered rows, compact
   int64_t* kv_slot = nullptr;      // [R][G*T]: cache slot offset of each gathered entry (KvDst)
-  // optional (T a multiple of 256): each loop's active row tiles (TileList),
-  // appended per sequence; the counts start at 0
-  int32_t* tile_cnt = nullptr;     // [R][3]: tiles of 64, 128 and 256 rows
-  int32_t* tile_list64 = nullptr;  // [R][G*T / 64]
-  int32_t* tile_list128 = nullptr; // [R][G*T / 128]
-  int32_t* tile_list256 = nullptr; // [R][G*T / 256]
+  int32_t* nact = nullptr;         // [R]: gathered rows of each loop
+  int32_t* seq_cnt = nullptr;      // [G][R]: gathered tokens of each sequence (scratch)
+  int32_t* row_off = nullptr;      // [G][R]: where the sequence's rows start
 };
 hipError_t launch_plan_prefill(const PrefillPlanArgs& a, hipStream_t s);
 
@@ -269,12 +279,14 @@ struct AttnPrefillArgs {
   CacheView c;
   int loop = 0, layer = 0, d = 0;
   int b0 = 0, G = 0, T = 0;
-  const float* q = nullptr; // [G*T][d], row g*T + a
-  float* o = nullptr;       // [G*T][d]
+  const int32_t* row_off = nullptr;  // [G][R]: first compact row of (sequence, loop)
+  const float* q = nullptr; // [rows][d], row row_off + a
+  float* o = nullptr;       // [rows][d], or
+  bf16* o16 = nullptr;      // o as operand rows of o_parts bf16 parts
+  int o_parts = 1;
   float scale_log2 = 0.f;
-  int q_single = 0;         // bf16 keys: the scaled q enters the score product as one bf16 part (not hi + lo)
-  bf16* o16 = nullptr;      // [G*T][d]: o written as bf16 instead of to o
-  const bf16* q16 = nullptr;  // with q_single: [G*T][d] q already scaled and rounded (bf16(q * scale_log2)), read in place of q
+  const bf16* q16 = nullptr;  // bf16 keys: [rows][d] q already scaled and rounded (bf16(q * scale_log2)),
+                              // read in place of q as one bf16 part (not hi + lo)
 };
 template <typename T> hipError_t launch_attn_prefill(const AttnPrefillArgs& a, hipStream_t s);
 

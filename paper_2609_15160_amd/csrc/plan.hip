@@ -240,103 +240,118 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_decode(DecodePlanArgs a) 
 }
 
 // ---------------------------------------------------------------------------
-// Prefill planner: workgroup g handles sequence b0 + g.  For each loop i it
-// gathers rho^(i) = sort(A_i) over the call's T tokens (Eq. 6) by a block
-// prefix sum over the flags m_t >= i, and places those n entries in slots
-// [n_old, n_old + n) of cache (b, i): n_old = 0 for a new batch, the current
-// length when the call continues the caches (a later prompt chunk).  The
-// partly filled last page is used first, then ceil-rounded new pages are
+// Prefill planner, first launch: workgroup g counts sequence b0 + g's tokens
+// per loop (those of depth >= i + 1) into seq_cnt[g][i].
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_plan_count(PrefillPlanArgs a) {
+  const int tid = threadIdx.x, g = blockIdx.x, T = a.T, R = a.c.R;
+  __shared__ int hist[kMaxLoops];
+  if (tid < kMaxLoops) hist[tid] = 0;
+  __syncthreads();
+  const int32_t* depth = a.depth + (int64_t)g * T;
+  for (int t0 = 0; t0 < T; t0 += 256 * 4) {
+    int m[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m[u] = depth[min(t0 + u * 256 + tid, T - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool in = t0 + u * 256 + tid < T;
+      for (int i = 0; i < R; ++i) {
+        const unsigned long long who = __ballot(in && m[u] == i + 1);
+        if (lane_id() == 0 && who) atomicAdd(&hist[i], __popcll(who));
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < R) {
+    int n = 0;
+    for (int i = tid; i < R; ++i) n += hist[i];
+    a.seq_cnt[g * R + tid] = n;
+    atomicAdd(&a.c.depth_hist[tid], (unsigned long long)hist[tid]);
+    if (tid == 0) a.c.seq_len[a.b0 + g] = a.pos0 + T;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Second launch: workgroup (g, i) gathers rho^(i) = sort(A_i) over sequence
+// b0 + g's T tokens (Eq. 6) by a prefix sum over the flags m_t >= i, into the
+// compact rows that follow the earlier sequences', and places those n entries
+// in slots [n_old, n_old + n) of cache (b, i): n_old = 0 for a new batch, the
+// current length when the call continues the caches (a later prompt chunk).
+// The partly filled last page is used first, then ceil-rounded new pages are
 // taken from the pool; every new slot records its original position
 // (Section 3.3 address translation).  chunk_len[b][i] = n.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kPlanThreads) void k_plan_prefill(PrefillPlanArgs a) {
+constexpr int kPrePlanThreads = 256, kPrePlanTokens = 4;
+
+__global__ __launch_bounds__(kPrePlanThreads) void k_plan_prefill(PrefillPlanArgs a) {
   const CacheView& c = a.c;
-  const int tid = threadIdx.x, g = blockIdx.x, T = a.T, R = c.R;
-  const int b = a.b0 + g;
+  const int tid = threadIdx.x, T = a.T, R = c.R;
+  const int g = blockIdx.x, i = blockIdx.y;
+  const int b = a.b0 + g, bi = b * R + i;
   const int64_t GT = (int64_t)a.G * T;
-  __shared__ int scan_tmp[kPlanThreads / kWave + 1];
-  __shared__ int s_carry, s_base, s_tiles[3];
-  __shared__ unsigned long long hist[kMaxLoops];
-  if (tid < kMaxLoops) hist[tid] = 0ull;
-  __syncthreads();
-  for (int t = tid; t < T; t += kPlanThreads) atomicAdd(&hist[a.depth[(int64_t)g * T + t] - 1], 1ull);
-  for (int i = 0; i < R; ++i) {
-    int32_t* idx = a.tok_idx + (int64_t)i * GT + (int64_t)g * T;
-    if (tid == 0) s_carry = 0;
-    __syncthreads();
-    for (int t0 = 0; t0 < T; t0 += kPlanThreads) {
-      const int t = t0 + tid;
-      const int f = (t < T && a.depth[(int64_t)g * T + t] >= i + 1) ? 1 : 0;
-      int tot;
-      const int ex = block_exclusive_scan(f, scan_tmp, &tot);
-      if (f) idx[s_carry + ex] = g * T + t;
-      __syncthreads();
-      if (tid == 0) s_carry += tot;
-      __syncthreads();
+  __shared__ int scan_tmp[kPrePlanThreads / kWave + 1];
+  __shared__ int s_base;
+  const int n = a.seq_cnt[g * R + i];
+  const int old = a.append ? c.cache_len[bi] : 0;
+  const int p_old = (old + kPage - 1) / kPage;           // pages already holding entries
+  const int np = (old + n + kPage - 1) / kPage - p_old;  // pages to take
+  if (tid == 0) {
+    int base = np > 0 ? atomicAdd(c.page_next, np) : 0;
+    if ((int64_t)base + np > c.max_pages) {
+      set_err(c.err, kErrOutOfPages);
+      base = -1;
     }
-    const int n = s_carry;
-    const int bi = b * R + i;
-    const int old = a.append ? c.cache_len[bi] : 0;
-    const int p_old = (old + kPage - 1) / kPage;        // pages already holding entries
-    const int np = (old + n + kPage - 1) / kPage - p_old; // pages to take
-    if (tid == 0) {
-      int base = np > 0 ? atomicAdd(c.page_next, np) : 0;
-      if ((int64_t)base + np > c.max_pages) {
-        set_err(c.err, kErrOutOfPages);
-        base = -1;
-      }
-      s_base = base;
-    }
-    __syncthreads();
-    const int base = s_base;
-    const int nn = base < 0 ? 0 : n;
-    int32_t* pt = c.page_table + (int64_t)bi * c.pages_per_seq;
-    if (base >= 0) {
-      for (int p = tid; p < np; p += kPlanThreads) pt[p_old + p] = base + p;
-      // tail of the partly filled page
-      const int tail = p_old * kPage - old;
-      if (tid < tail && tid < n) {
-        const int s = old + tid;
-        c.pos[(int64_t)pt[s / kPage] * kPage + s % kPage] = a.pos0 + idx[tid] - g * T;
-      }
-      // whole new pages; slots past the last entry are marked empty
-      for (int s = tid; s < np * kPage; s += kPlanThreads) {
-        const int e = p_old * kPage + s - old;  // entry index within the call
-        c.pos[(int64_t)base * kPage + s] = e < n ? a.pos0 + idx[e] - g * T : -1;
-      }
-    }
-    // the cache slot offset of every gathered entry, for the QKV epilogue:
-    // entry e goes to slot old + e, on the partly filled last page or on new
-    // page base + (page index - p_old)
-    int64_t* ks = a.kv_slot + (int64_t)i * GT + (int64_t)g * T;
-    for (int e = tid; e < n; e += kPlanThreads) {
-      const int s = old + e, pi = s / kPage;
-      const int page = base < 0 ? -1 : pi < p_old ? pt[pi] : base + (pi - p_old);
-      ks[e] = page < 0 || page >= c.max_pages ? -1 : (int64_t)page * c.page_elems + s % kPage;
-    }
-    if (a.tile_cnt) {
-      // this sequence's active row tiles of loop i: rows g T + k BM, k < ceil(nn / BM)
-      const int t64 = (nn + 63) / 64, t128 = (nn + 127) / 128, t256 = (nn + 255) / 256;
-      if (tid == 0) {
-        s_tiles[0] = atomicAdd(&a.tile_cnt[i * 3 + 0], t64);
-        s_tiles[1] = atomicAdd(&a.tile_cnt[i * 3 + 1], t128);
-        s_tiles[2] = atomicAdd(&a.tile_cnt[i * 3 + 2], t256);
-      }
-      __syncthreads();
-      for (int k = tid; k < t64; k += kPlanThreads) a.tile_list64[(int64_t)i * (GT / 64) + s_tiles[0] + k] = g * T + k * 64;
-      for (int k = tid; k < t128; k += kPlanThreads)
-        a.tile_list128[(int64_t)i * (GT / 128) + s_tiles[1] + k] = g * T + k * 128;
-      for (int k = tid; k < t256; k += kPlanThreads)
-        a.tile_list256[(int64_t)i * (GT / 256) + s_tiles[2] + k] = g * T + k * 256;
-    }
-    if (tid == 0) {
-      c.cache_len[bi] = old + nn;
-      c.chunk_len[bi] = nn;
-    }
-    __syncthreads();
+    s_base = base;
   }
-  if (tid == 0) c.seq_len[b] = a.pos0 + T;
-  if (tid < R) atomicAdd(&c.depth_hist[tid], hist[tid]);
+  // rows of the earlier sequences
+  int before = 0;
+  for (int gg = tid; gg < g; gg += kPrePlanThreads) before += a.seq_cnt[gg * R + i];
+  int off;
+  block_exclusive_scan(before, scan_tmp, &off);  // (a barrier: s_base is written)
+  const int base = s_base;
+  int32_t* pt = c.page_table + (int64_t)bi * c.pages_per_seq;
+  // the partly filled last page (base >= 0 or not, its slots are the cache's own)
+  const int last_page = old % kPage != 0 ? pt[p_old - 1] : -1;
+  int32_t* idx = a.tok_idx + (int64_t)i * GT + off;
+  int64_t* ks = a.kv_slot + (int64_t)i * GT + off;
+  const int32_t* depth = a.depth + (int64_t)g * T;
+  int e0 = 0;
+  for (int t0 = 0; t0 < T; t0 += kPrePlanThreads * kPrePlanTokens) {
+    const int tb = t0 + tid * kPrePlanTokens;
+    int f[kPrePlanTokens], cnt = 0, tot;
+#pragma unroll
+    for (int u = 0; u < kPrePlanTokens; ++u) {
+      const int m = depth[min(tb + u, T - 1)];
+      f[u] = tb + u < T && m > i;
+      cnt += f[u];
+    }
+    int e = e0 + block_exclusive_scan(cnt, scan_tmp, &tot);
+#pragma unroll
+    for (int u = 0; u < kPrePlanTokens; ++u) {
+      if (!f[u]) continue;
+      const int s = old + e, pi = s / kPage;
+      const int page = base < 0 ? -1 : pi < p_old ? last_page : base + (pi - p_old);
+      idx[e] = g * T + tb + u;
+      ks[e] = page < 0 ? -1 : (int64_t)page * c.page_elems + s % kPage;
+      if (page >= 0) c.pos[(int64_t)page * kPage + s % kPage] = a.pos0 + tb + u;
+      ++e;
+    }
+    e0 += tot;
+  }
+  if (base >= 0) {
+    for (int p = tid; p < np; p += kPrePlanThreads) pt[p_old + p] = base + p;
+    // slots of the last new page past the last entry are marked empty
+    const int s = old + n + tid;
+    if (np > 0 && tid < kPage && s < (p_old + np) * kPage) c.pos[(int64_t)(base + np - 1) * kPage + s % kPage] = -1;
+  }
+  if (tid == 0) {
+    const int nn = base < 0 ? 0 : n;
+    c.cache_len[bi] = old + nn;
+    c.chunk_len[bi] = nn;
+    a.row_off[g * R + i] = off;
+    if (g == a.G - 1) a.nact[i] = off + n;
+  }
 }
 
 __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
@@ -381,9 +396,9 @@ hipError_t launch_plan_decode(const DecodePlanArgs& a, hipStream_t s) {
 
 hipError_t launch_plan_prefill(const PrefillPlanArgs& a, hipStream_t s) {
   if (a.G <= 0) return hipSuccess;
-  if (a.tile_cnt && (a.T % 256 != 0 || !a.tile_list64 || !a.tile_list128 || !a.tile_list256))
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_plan_prefill, dim3(a.G), dim3(kPlanThreads), 0, s, a);
+  if (!a.nact || !a.seq_cnt || !a.row_off) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_plan_count, dim3(a.G), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_plan_prefill, dim3(a.G, a.c.R), dim3(kPrePlanThreads), 0, s, a);
   return hipGetLastError();
 }
 

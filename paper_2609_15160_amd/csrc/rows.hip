@@ -147,12 +147,12 @@ __global__ __launch_bounds__(256) void k_embed_route(EmbedArgs a) {
     }
   }
   if (a.y16) {
-    bf16* y = a.y16 + (int64_t)row * a.d;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int k = 4 * lane + 256 * c;
-      const float4 v = scale4(h[c], inv);
-      if (k < a.d) *reinterpret_cast<uint2*>(y + k) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+      if (k >= a.d) continue;
+      if (a.parts == 2) store_operand4<2>(a.y16, row, k, a.d, scale4(h[c], inv));
+      else store_operand4<1>(a.y16, row, k, a.d, scale4(h[c], inv));
     }
   }
   if (!a.route) return;  // the MLP router runs after this kernel
@@ -264,14 +264,20 @@ __global__ __launch_bounds__(256) void k_resid_norm(ResidNormArgs a) {
       }
   }
   if (a.y16) {
-    bf16* y16 = a.y16 + (int64_t)src * a.d;
+    const float* gm = a.mod_g ? a.mod_g + (int64_t)(a.mod_depth[src] - 1) * a.mod_ld : nullptr;
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         const int k = 4 * (lane + 64 * v) + 1024 * c;
-        const float4 hv = scale4(h[v][c], inv);
-        if (k < a.d) *reinterpret_cast<uint2*>(y16 + k) = make_uint2(pack_bf16x2(hv.x, hv.y), pack_bf16x2(hv.z, hv.w));
+        if (k >= a.d) continue;
+        float4 hv = scale4(h[v][c], inv);
+        if (gm) {
+          const float4 gv = V4<float>::load(gm + k);
+          hv = make_float4(hv.x * (1.f + gv.x), hv.y * (1.f + gv.y), hv.z * (1.f + gv.z), hv.w * (1.f + gv.w));
+        }
+        if (a.parts == 2) store_operand4<2>(a.y16, src, k, a.d, hv);
+        else store_operand4<1>(a.y16, src, k, a.d, hv);
       }
   }
 }

@@ -449,6 +449,25 @@ def test_bf16_prefill_single_part_activations_d768():
     _check_bf16(m, w, prompts, g, o, sample, "bf16-prefill-one-part-d768")
 
 
+@pytest.mark.parametrize("act16", [False, True], ids=["two-parts", "one-part"])
+@pytest.mark.parametrize("batch,prompt_len", [(1, 65), (2, 33), (3, 43), (5, 26), (2, 256), (9, 151)])
+def test_bf16_prefill_row_tile_edges(batch, prompt_len, act16):
+    """Compact rows of the prefill projections around the tile edges (65, 66,
+    129, 130, 512 and 1359 rows in the first loop, ragged counts in the later
+    ones, sequences that share a tile), a vocabulary that fits no tile and a
+    one-tile model width: every position's logits and two decode steps against
+    the oracle, every cache index."""
+    m = synth.ModelConfig("bf16-d128", "bf16", vocab=509, d_model=128, n_heads=2, head_dim=64, d_ff=384,
+                          n_layers=2, max_loops=5, batch=batch, prompt_len=prompt_len, steps=2,
+                          router_bias="calibrated")
+    w = synth.make_weights(m)
+    prompts = synth.make_prompts(m)
+    sample = list(range(batch))
+    g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, all_logits=True, prefill_act_bf16=act16)
+    o = parity.run_oracle(m, w, prompts, g.step_tokens, all_logits=True)
+    _check_bf16(m, w, prompts, g, o, sample, f"bf16-row-tiles-{batch}x{prompt_len}-{act16}")
+
+
 def test_bf16_prefill_single_part_ragged_wide_tiles():
     """One-part bf16 prefill activations on a model whose widths leave ragged
     256-column tiles (d 640 = 5 x 128 heads, QKV 1920 columns, SwiGLU 1664)
