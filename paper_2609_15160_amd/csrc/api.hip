@@ -21,7 +21,7 @@ enum Buf {
   B_POOL, B_POS, B_PAGE_TABLE, B_CACHE_LEN, B_CHUNK_LEN, B_SEQ_LEN, B_SCALARS, B_DEPTH_HIST, B_STEP_STATS,
   B_X_DEC, B_XC_DEC, B_KVSLOT, B_DEPTH_DEC, B_PERM, B_NACT, B_Q_DEC, B_O_DEC, B_ACT_DEC, B_KEYS,
   B_X_PRE, B_Y_PRE, B_DEPTH_PRE, B_TOK_IDX, B_KVSLOT_PRE, B_Q_PRE, B_O_PRE, B_ACT_PRE, B_HID,
-  B_ROW_DEPTH, B_MOD, B_COND_TMP, B_WFRAG, B_PRE_NACT, B_PRE_CNT, B_PRE_OFF,
+  B_ROW_DEPTH, B_MOD, B_COND_TMP, B_WFRAG, B_PRE_NACT, B_PRE_CNT, B_PRE_OFF, B_SSQ,
   B_COUNT
 };
 
@@ -32,6 +32,10 @@ struct Layout {
   int64_t page_elems = 0;
   int pages_per_seq = 0, pre_rows = 0, s = 0;
 };
+
+// Prefill groups of at most this many rows fuse the RMSNorm into the
+// projections that read it.
+constexpr int kPrefillFusedNormRows = 4096;
 
 bool make_layout(const tlf_config& c, Layout* L) {
   const int64_t s = c.dtype == TLF_DTYPE_BF16 ? 2 : 4;
@@ -62,7 +66,7 @@ bool make_layout(const tlf_config& c, Layout* L) {
   sz[B_ACT_DEC] = (int64_t)((B + 15) / 16 * 16) * F * 4;  // whole groups of 16 rows (fragment order)
   sz[B_KEYS] = B * ceil_div(c.vocab, kWave) * 8;  // greedy key per 64-column group of each row
   sz[B_X_PRE] = P * d * 4;
-  sz[B_Y_PRE] = P * d * 4;  // float32 rows, or (bf16 models) operand rows of one or two bf16 parts
+  sz[B_Y_PRE] = P * d * 4;  // RMSNorm(x) in float32, or (bf16 models) the operand rows of one or two bf16 parts
   sz[B_DEPTH_PRE] = P * 4;
   sz[B_TOK_IDX] = R * P * 4;
   sz[B_KVSLOT_PRE] = R * P * 8;
@@ -81,6 +85,9 @@ bool make_layout(const tlf_config& c, Layout* L) {
   sz[B_PRE_NACT] = R * 4;
   sz[B_PRE_CNT] = B * R * 4;
   sz[B_PRE_OFF] = B * R * 4;
+  // rows' sums of squares where the prefill projections take the norm
+  sz[B_SSQ] = c.dtype == TLF_DTYPE_BF16 && !c.adaln && d <= kNormMaxWidth
+                  ? std::min<int64_t>(P, kPrefillFusedNormRows) * (d / 32) * 4 : 0;
   size_t off = 0;
   for (int i = 0; i < B_COUNT; ++i) {
     if (sz[i] < 0) return false;
@@ -174,6 +181,7 @@ struct tlf_ctx {
   bool prefilled = false, poisoned = false;
   int sticky = TLF_OK;
   int cus = 0;  // compute units of the device
+  PgemmShapes shapes[5];  // prefill tile shapes of the QKV, O, gate/up and down projections and the LM head
   int attn_blocks[2] = {1, 1};  // resident decode-attention workgroups per CU (4 and 8 waves)
   // measurement: event pairs around decode-attention launches, resolved by tlf_cache_stats
   bool profiling = false;     // decode steps launched eagerly, block region timed
@@ -336,10 +344,16 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     // one short sequence: the projections take the split-K decode GEMM with
     // the RMSNorm fused (x is read through the gathered positions, no y)
     const bool few = Gc == 1 && T_ <= kPrefillFewRows;
-    // bf16 models: RMSNorm(x), o and act are handed on as bf16 operand rows of
-    // two parts, or of one (prefill_act_bf16); the LM head always takes two
+    // bf16 models: x, o and act are handed on as bf16 operand rows of two
+    // parts, or of one (prefill_act_bf16), and the projections normalise x;
+    // the LM head always takes two parts
     const bool parted = c.dtype == TLF_DTYPE_BF16 && !few;
     const int parts = c.prefill_act_bf16 ? 1 : 2;
+    // with AdaLN the operand is RMSNorm(x) (1 + gamma), and with many rows the
+    // extra operand rows cost the residual projections as much as the kernel
+    // saves: then a norm kernel writes the normalised operand after each of them
+    const bool fused = parted && !c.adaln && rows <= kPrefillFusedNormRows && ctx->L.size[B_SSQ] > 0;
+    float* ssq = fused ? ctx->buf<float>(B_SSQ) : nullptr;
     bf16* y16 = parted ? ctx->buf<bf16>(B_Y_PRE) : nullptr;
     bf16* o16 = parted ? ctx->buf<bf16>(B_O_PRE) : nullptr;
     bf16* act16 = parted ? ctx->buf<bf16>(B_ACT_PRE) : nullptr;
@@ -347,7 +361,8 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     ea.tok_emb = ctx->w.tok_emb; ea.pos_emb = ctx->w.pos_emb; ea.Wr = ctx->w.router_w; ea.br = ctx->w.router_b;
     ea.tokens = tokens + (int64_t)b0 * T_;
     ea.rows = rows; ea.V = c.vocab; ea.d = d; ea.R = R; ea.prefill_T = T_; ea.pos0 = pos0;
-    ea.x = x; ea.y = few || parted ? nullptr : y; ea.y16 = c.adaln ? nullptr : y16; ea.parts = parts; ea.eps = c.rms_eps;
+    ea.x = x; ea.y = few || parted ? nullptr : y; ea.x16 = fused ? y16 : nullptr; ea.ssq = ssq; ea.parts = parts;
+    ea.y16 = parted && !fused && !c.adaln ? y16 : nullptr; ea.eps = c.rms_eps;
     ea.depth = ctx->buf<int32_t>(B_DEPTH_PRE);
     ea.out_depth = depths ? depths + (int64_t)b0 * T_ : nullptr;
     ea.rule = c.route_rule; ea.threshold = c.route_threshold; ea.fixed = c.fixed_depth;
@@ -368,7 +383,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     pa.row_off = ctx->buf<int32_t>(B_PRE_OFF);
     TLF_HIP(launch_plan_prefill(pa, s));
 
-    // RMSNorm(x) after a residual projection, for the projection at (loop ni,
+    // float32 or AdaLN models: RMSNorm(x) after a residual projection, for the projection at (loop ni,
     // layer nj) that reads it next: with operand rows its AdaLN scale (table
     // part 2 QKV, 3 gate/up) is applied here
     ResidNormArgs rn;
@@ -390,7 +405,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     }
     auto project = [&](const GemmArgs& g, AKind ak, EKind ek) {
       if (few) return launch_dgemm<T>(g, ak, ek, ek == E_QKV || ek == E_SWIGLU, ctx->cus, s);
-      if (parted) return launch_pgemm(g, ak, ek, parts, ctx->cus, s);
+      if (parted) return launch_pgemm(g, ak, ek, fused && ek != E_RESID, parts, ctx->cus, s);
       return launch_gemm<T>(g, ak, ek, false, s);
     };
 
@@ -406,6 +421,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         q.A = few ? x : y; q.lda = d; q.W = lw.w_qkv; q.Wf = ctx->wfrag(j, 0); q.N = 3 * d; q.K = d; q.w_rows = 3 * d; q.rm = rm;
         q.out = ctx->buf<float>(B_Q_PRE); q.ldo = d; q.d = d; q.eps = c.rms_eps; q.spec = i == 0;
         q.kv.c = ctx->cv; q.kv.loop = i; q.kv.layer = j; q.kv.slot_base = ctx->buf<int64_t>(B_KVSLOT_PRE) + (int64_t)i * rows;
+        q.shapes = ctx->shapes[0]; q.ssq = ssq;
         if (parted) q.A16 = y16;
         else set_mod(ctx, &q, i, j, 2, pre_depth, 1);
         const float scale_log2 = 1.4426950408889634f / std::sqrt((float)c.head_dim);
@@ -426,14 +442,15 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         GemmArgs o;
         o.A = ctx->buf<float>(B_O_PRE); o.lda = d; o.W = lw.w_o; o.Wf = ctx->wfrag(j, 1); o.N = d; o.K = d; o.w_rows = d; o.rm = rm;
         o.out = x; o.ldo = d; o.scatter = 1; o.spec = i == 0; o.A16 = o16;
+        o.shapes = ctx->shapes[1]; o.out16 = fused ? y16 : nullptr; o.ssq = ssq;
         set_mod(ctx, &o, i, j, 0, pre_depth, 1);
         TLF_HIP(project(o, A_CMP, E_RESID));
-        if (!few) TLF_HIP(norm(rm, i, j, 3));
+        if (!few && !fused) TLF_HIP(norm(rm, i, j, 3));
 
         GemmArgs gu;
         gu.A = few ? x : y; gu.lda = d; gu.W = lw.w_gate_up; gu.Wf = ctx->wfrag(j, 2); gu.N = 2 * F; gu.K = d; gu.w_rows = 2 * F; gu.rm = rm;
         gu.out = ctx->buf<float>(B_ACT_PRE); gu.ldo = F; gu.F = F; gu.eps = c.rms_eps; gu.spec = i == 0;
-        gu.out16 = act16;
+        gu.out16 = act16; gu.shapes = ctx->shapes[2]; gu.ssq = ssq;
         if (parted) gu.A16 = y16;
         else set_mod(ctx, &gu, i, j, 3, pre_depth, 1);
         TLF_HIP(project(gu, A_SRC, E_SWIGLU));
@@ -441,10 +458,11 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         GemmArgs dn;
         dn.A = ctx->buf<float>(B_ACT_PRE); dn.lda = F; dn.W = lw.w_down; dn.Wf = ctx->wfrag(j, 3); dn.N = d; dn.K = F; dn.w_rows = d;
         dn.rm = rm; dn.out = x; dn.ldo = d; dn.scatter = 1; dn.spec = i == 0; dn.A16 = act16;
+        dn.shapes = ctx->shapes[3]; dn.out16 = fused ? y16 : nullptr; dn.ssq = ssq;
         set_mod(ctx, &dn, i, j, 1, pre_depth, 1);
         TLF_HIP(project(dn, A_CMP, E_RESID));
         const bool last = j + 1 == c.n_layers;
-        if (!few) TLF_HIP(norm(rm, last ? i + 1 : i, last ? 0 : j + 1, 2));
+        if (!few && !fused) TLF_HIP(norm(rm, last ? i + 1 : i, last ? 0 : j + 1, 2));
       }
     }
     GemmArgs hd;
@@ -460,12 +478,13 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     if (hd.rm.rows < kHeadGemmRows) {  // few rows: the norm fused
       TLF_HIP(launch_dgemm<T>(hd, A_SRC, E_LOGITS, true, ctx->cus, s));
     } else if (parted) {
+      const bool hn = fused && parts == 2;
       if (parts == 1 || c.adaln) {  // y16 holds one part, or the last projection's scale
         rn.parts = 2;
         TLF_HIP(norm(hd.rm, R, 0, 2));
       }
-      hd.A16 = y16;
-      TLF_HIP(launch_pgemm(hd, A_SRC, E_LOGITS, 2, ctx->cus, s));
+      hd.A16 = y16; hd.shapes = ctx->shapes[4]; hd.ssq = ssq;
+      TLF_HIP(launch_pgemm(hd, A_SRC, E_LOGITS, hn, 2, ctx->cus, s));
     } else {
       hd.A = y;
       TLF_HIP(launch_gemm<T>(hd, A_SRC, E_LOGITS, false, s));
@@ -658,6 +677,11 @@ int tlf_init(const tlf_config* cfg, const tlf_weights* w, void* d_workspace, siz
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) { delete ctx; return TLF_E_HIP; }
   ctx->cus = std::max(1, cus);
+  {
+    const int d = cfg->d_model, F = cfg->d_ff, parts = cfg->prefill_act_bf16 ? 1 : 2;
+    const int N[5] = {3 * d, d, 2 * F, d, cfg->vocab}, K[5] = {d, d, d, F, d};
+    for (int k = 0; k < 5; ++k) ctx->shapes[k] = pgemm_shapes(N[k], K[k], k < 4 ? parts : 2, ctx->cus, L.pre_rows);
+  }
   for (int k = 0; k < 2 && e == hipSuccess; ++k) {
     int blocks = 0;
     e = cfg->dtype == TLF_DTYPE_BF16 ? attn_decode_blocks_per_cu<bf16>(cfg->head_dim, 4 << k, &blocks)

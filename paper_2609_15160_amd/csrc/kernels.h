@@ -52,6 +52,13 @@ enum AKind { A_SRC = 0, A_CMP = 1 };
 // (the MLP router's hidden layer).
 enum EKind { E_QKV = 0, E_RESID = 1, E_SWIGLU = 3, E_LOGITS = 4, E_HIDDEN = 5 };
 
+// Tile shape of the prefill projections by row count, worked out once per
+// projection (pgemm_shapes): runs of (last row count << 3 | shape), ascending.
+constexpr int kShapeRuns = 12;
+struct PgemmShapes {
+  int32_t run[kShapeRuns] = {};
+};
+
 struct GemmArgs {
   const float* A = nullptr; // float32 rows
   int lda = 0;
@@ -95,9 +102,13 @@ struct GemmArgs {
   const int32_t* keep_depth = nullptr;  // E_RESID (dense decode): row r is stored only while
   int keep_loop = 0;                    // keep_depth[r] > keep_loop (its token runs this loop)
   const bf16* A16 = nullptr;  // launch_pgemm: the operand rows in one or two bf16 parts (operand_off)
-  bf16* out16 = nullptr;      // launch_pgemm E_SWIGLU: act as operand rows of the same number of parts
+  bf16* out16 = nullptr;      // launch_pgemm: act (E_SWIGLU), or the new residual (E_RESID, may be nullptr), as
+                              // operand rows of the same number of parts
   bf16* q16 = nullptr;        // launch_pgemm E_QKV, one part: q rows written as bf16(q * q_scale) instead of to out
   float q_scale = 1.f;
+  float* ssq = nullptr;       // launch_pgemm: each row's sums of squares in parts of 32 columns, [rows][K / 32], read
+                              // with norm; E_RESID with out16: written, [rows][N / 32]
+  PgemmShapes shapes;         // launch_pgemm: pgemm_shapes of this N, K and number of parts
 };
 
 // Offset of element (R, k) of a [rows][K] operand stored in MFMA fragment order.
@@ -128,8 +139,12 @@ template <int P> __device__ __forceinline__ void store_operand4(bf16* p, int64_t
 
 // Prefill projections of bf16 models (pgemm.hip): A as bf16 operand rows of
 // `parts` parts, weights in fragment order (the LM head's row-major).
-// Supported: (A_SRC, E_QKV | E_SWIGLU | E_LOGITS), (A_CMP, E_RESID).
-hipError_t launch_pgemm(const GemmArgs& a, AKind ak, EKind ek, int parts, int cus, hipStream_t s);
+// Supported: (A_SRC, E_QKV | E_SWIGLU | E_LOGITS, norm or not), (A_CMP,
+// E_RESID, no norm).  norm: the rows hold the residual x and the product is
+// taken with RMSNorm(x).
+constexpr int kNormMaxWidth = 1024;  // widest rows of launch_pgemm's norm
+hipError_t launch_pgemm(const GemmArgs& a, AKind ak, EKind ek, bool norm, int parts, int cus, hipStream_t s);
+PgemmShapes pgemm_shapes(int N, int K, int parts, int cus, int max_rows);
 // Many-row projections of float32 models, the MLP router's hidden layer and
 // the decode LM head of a large batch: MFMA tiles staged through LDS.  norm:
 // A is the residual x and the product is taken with RMSNorm(x) (supported for
@@ -175,7 +190,9 @@ struct EmbedArgs {
   const int32_t* seq_len = nullptr;
   float* x = nullptr;             // [rows][d] float residual
   float* y = nullptr;             // [rows][d] RMSNorm(x), or nullptr
-  bf16* y16 = nullptr;            // RMSNorm(x) as operand rows of `parts` bf16 parts, or nullptr
+  bf16* x16 = nullptr;            // x as operand rows of `parts` bf16 parts, or nullptr
+  bf16* y16 = nullptr;            // RMSNorm(x) as such rows, or nullptr (not with x16)
+  float* ssq = nullptr;           // with x16: the rows' sums of squares, [rows][d / 32] (the first, then zeros)
   int parts = 1;
   float eps = 1e-5f;
   int32_t* depth = nullptr;       // [rows]

@@ -136,23 +136,28 @@ __global__ __launch_bounds__(256) void k_embed_route(EmbedArgs a) {
     const int k = 4 * lane + 256 * c;
     if (k < a.d) V4<float>::store(x + k, h[c]);
   }
+  float inv = 1.f;
   ss = wave_sum(ss);
-  const float inv = rsqrtf(ss / (float)a.d + a.eps);
+  if (a.y || a.y16) inv = rsqrtf(ss / (float)a.d + a.eps);
+  if (a.ssq)
+    for (int k = lane; k < a.d / 32; k += kWave) a.ssq[(int64_t)row * (a.d / 32) + k] = k == 0 ? ss : 0.f;
+  if (a.x16 || a.y16) {
+    bf16* o16 = a.x16 ? a.x16 : a.y16;
+    const float sc = a.x16 ? 1.f : inv;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int k = 4 * lane + 256 * c;
+      if (k >= a.d) continue;
+      if (a.parts == 2) store_operand4<2>(o16, row, k, a.d, scale4(h[c], sc));
+      else store_operand4<1>(o16, row, k, a.d, scale4(h[c], sc));
+    }
+  }
   if (a.y) {
     float* y = a.y + (int64_t)row * a.d;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int k = 4 * lane + 256 * c;
       if (k < a.d) V4<float>::store(y + k, scale4(h[c], inv));
-    }
-  }
-  if (a.y16) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int k = 4 * lane + 256 * c;
-      if (k >= a.d) continue;
-      if (a.parts == 2) store_operand4<2>(a.y16, row, k, a.d, scale4(h[c], inv));
-      else store_operand4<1>(a.y16, row, k, a.d, scale4(h[c], inv));
     }
   }
   if (!a.route) return;  // the MLP router runs after this kernel
