@@ -181,7 +181,7 @@ struct tlf_ctx {
   bool prefilled = false, poisoned = false;
   int sticky = TLF_OK;
   int cus = 0;  // compute units of the device
-  PgemmShapes shapes[5];  // prefill tile shapes of the QKV, O, gate/up and down projections and the LM head
+  PgemmShapes shapes[2][5];  // prefill tile shapes with one and two parts: QKV, O, gate/up, down, LM head
   int attn_blocks[2] = {1, 1};  // resident decode-attention workgroups per CU (4 and 8 waves)
   // measurement: event pairs around decode-attention launches, resolved by tlf_cache_stats
   bool profiling = false;     // decode steps launched eagerly, block region timed
@@ -301,9 +301,17 @@ int attn_waves(const tlf_ctx* ctx) {
 // Decode batches of at least this many rows run the LM head on the 128 x 128 GEMM.
 constexpr int kHeadGemmRows = 128;
 
-// Prefill of a single sequence of at most this many tokens runs its
-// projections on the split-K decode GEMM.
-constexpr int kPrefillFewRows = 64;
+// bf16 prefill groups of at most this many row elements (rows x d_model) run
+// their projections on the split-K decode GEMM, which reads every row once per
+// column tile: one 768-wide sequence of 140, 230 and 300 tokens took 651, 715
+// and 795 us per prefill on it against 699, 735 and 762 us on launch_pgemm, a
+// 2048-wide one of 200 tokens 1832 against 1581 us.
+constexpr int64_t kPrefillFewElems = 256 * 768;
+constexpr int kPrefillFewRowsF32 = 2048;  // float32 models: a single sequence of at most this many tokens
+
+// A single sequence of at most this many tokens keeps two bf16 parts per
+// activation whatever prefill_act_bf16 says.
+constexpr int kPrefillTwoPartTokens = 2048;
 
 // AdaLN: point a projection at its rows' modulation at (loop i, layer j):
 // part 0..3 = alpha_msa, alpha_mlp, gamma_msa, gamma_mlp of the table
@@ -341,14 +349,16 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
   for (int b0 = 0; b0 < B; b0 += G) {
     const int Gc = std::min(G, B - b0);
     const int rows = Gc * T_;
-    // one short sequence: the projections take the split-K decode GEMM with
-    // the RMSNorm fused (x is read through the gathered positions, no y)
-    const bool few = Gc == 1 && T_ <= kPrefillFewRows;
+    // few rows: the projections take the split-K decode GEMM with the RMSNorm
+    // fused (x is read through the gathered positions, no y)
+    const bool few = c.dtype == TLF_DTYPE_BF16 ? (int64_t)rows * d <= kPrefillFewElems
+                                               : Gc == 1 && T_ <= kPrefillFewRowsF32;
     // bf16 models: x, o and act are handed on as bf16 operand rows of two
     // parts, or of one (prefill_act_bf16), and the projections normalise x;
     // the LM head always takes two parts
     const bool parted = c.dtype == TLF_DTYPE_BF16 && !few;
-    const int parts = c.prefill_act_bf16 ? 1 : 2;
+    const int parts = c.prefill_act_bf16 && !(Gc == 1 && T_ <= kPrefillTwoPartTokens) ? 1 : 2;
+    const PgemmShapes* shapes = ctx->shapes[parts - 1];
     // with AdaLN the operand is RMSNorm(x) (1 + gamma), and with many rows the
     // extra operand rows cost the residual projections as much as the kernel
     // saves: then a norm kernel writes the normalised operand after each of them
@@ -421,7 +431,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         q.A = few ? x : y; q.lda = d; q.W = lw.w_qkv; q.Wf = ctx->wfrag(j, 0); q.N = 3 * d; q.K = d; q.w_rows = 3 * d; q.rm = rm;
         q.out = ctx->buf<float>(B_Q_PRE); q.ldo = d; q.d = d; q.eps = c.rms_eps; q.spec = i == 0;
         q.kv.c = ctx->cv; q.kv.loop = i; q.kv.layer = j; q.kv.slot_base = ctx->buf<int64_t>(B_KVSLOT_PRE) + (int64_t)i * rows;
-        q.shapes = ctx->shapes[0]; q.ssq = ssq;
+        q.shapes = shapes[0]; q.ssq = ssq;
         if (parted) q.A16 = y16;
         else set_mod(ctx, &q, i, j, 2, pre_depth, 1);
         const float scale_log2 = 1.4426950408889634f / std::sqrt((float)c.head_dim);
@@ -432,7 +442,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
 
         AttnPrefillArgs at;
         at.c = ctx->cv; at.loop = i; at.layer = j; at.d = d; at.b0 = b0; at.G = Gc; at.T = T_;
-        at.row_off = pa.row_off;
+        at.row_off = pa.row_off; at.cus = ctx->cus;
         at.q = ctx->buf<float>(B_Q_PRE); at.o = ctx->buf<float>(B_O_PRE);
         at.scale_log2 = scale_log2;
         at.q16 = q16;
@@ -442,7 +452,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         GemmArgs o;
         o.A = ctx->buf<float>(B_O_PRE); o.lda = d; o.W = lw.w_o; o.Wf = ctx->wfrag(j, 1); o.N = d; o.K = d; o.w_rows = d; o.rm = rm;
         o.out = x; o.ldo = d; o.scatter = 1; o.spec = i == 0; o.A16 = o16;
-        o.shapes = ctx->shapes[1]; o.out16 = fused ? y16 : nullptr; o.ssq = ssq;
+        o.shapes = shapes[1]; o.out16 = fused ? y16 : nullptr; o.ssq = ssq;
         set_mod(ctx, &o, i, j, 0, pre_depth, 1);
         TLF_HIP(project(o, A_CMP, E_RESID));
         if (!few && !fused) TLF_HIP(norm(rm, i, j, 3));
@@ -450,7 +460,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         GemmArgs gu;
         gu.A = few ? x : y; gu.lda = d; gu.W = lw.w_gate_up; gu.Wf = ctx->wfrag(j, 2); gu.N = 2 * F; gu.K = d; gu.w_rows = 2 * F; gu.rm = rm;
         gu.out = ctx->buf<float>(B_ACT_PRE); gu.ldo = F; gu.F = F; gu.eps = c.rms_eps; gu.spec = i == 0;
-        gu.out16 = act16; gu.shapes = ctx->shapes[2]; gu.ssq = ssq;
+        gu.out16 = act16; gu.shapes = shapes[2]; gu.ssq = ssq;
         if (parted) gu.A16 = y16;
         else set_mod(ctx, &gu, i, j, 3, pre_depth, 1);
         TLF_HIP(project(gu, A_SRC, E_SWIGLU));
@@ -458,7 +468,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         GemmArgs dn;
         dn.A = ctx->buf<float>(B_ACT_PRE); dn.lda = F; dn.W = lw.w_down; dn.Wf = ctx->wfrag(j, 3); dn.N = d; dn.K = F; dn.w_rows = d;
         dn.rm = rm; dn.out = x; dn.ldo = d; dn.scatter = 1; dn.spec = i == 0; dn.A16 = act16;
-        dn.shapes = ctx->shapes[3]; dn.out16 = fused ? y16 : nullptr; dn.ssq = ssq;
+        dn.shapes = shapes[3]; dn.out16 = fused ? y16 : nullptr; dn.ssq = ssq;
         set_mod(ctx, &dn, i, j, 1, pre_depth, 1);
         TLF_HIP(project(dn, A_CMP, E_RESID));
         const bool last = j + 1 == c.n_layers;
@@ -475,7 +485,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
       hd.rm.rows = Gc; hd.rm.src_stride = T_; hd.rm.src_off = T_ - 1;
       hd.out_row_off = b0;
     }
-    if (hd.rm.rows < kHeadGemmRows) {  // few rows: the norm fused
+    if (few || hd.rm.rows < kHeadGemmRows) {  // the norm fused
       TLF_HIP(launch_dgemm<T>(hd, A_SRC, E_LOGITS, true, ctx->cus, s));
     } else if (parted) {
       const bool hn = fused && parts == 2;
@@ -483,7 +493,7 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         rn.parts = 2;
         TLF_HIP(norm(hd.rm, R, 0, 2));
       }
-      hd.A16 = y16; hd.shapes = ctx->shapes[4]; hd.ssq = ssq;
+      hd.A16 = y16; hd.shapes = ctx->shapes[1][4]; hd.ssq = ssq;
       TLF_HIP(launch_pgemm(hd, A_SRC, E_LOGITS, hn, 2, ctx->cus, s));
     } else {
       hd.A = y;
@@ -678,9 +688,10 @@ int tlf_init(const tlf_config* cfg, const tlf_weights* w, void* d_workspace, siz
   if (e != hipSuccess) { delete ctx; return TLF_E_HIP; }
   ctx->cus = std::max(1, cus);
   {
-    const int d = cfg->d_model, F = cfg->d_ff, parts = cfg->prefill_act_bf16 ? 1 : 2;
+    const int d = cfg->d_model, F = cfg->d_ff;
     const int N[5] = {3 * d, d, 2 * F, d, cfg->vocab}, K[5] = {d, d, d, F, d};
-    for (int k = 0; k < 5; ++k) ctx->shapes[k] = pgemm_shapes(N[k], K[k], k < 4 ? parts : 2, ctx->cus, L.pre_rows);
+    for (int p = 1; p <= 2; ++p)
+      for (int k = 0; k < 5; ++k) ctx->shapes[p - 1][k] = pgemm_shapes(N[k], K[k], p, ctx->cus, L.pre_rows);
   }
   for (int k = 0; k < 2 && e == hipSuccess; ++k) {
     int blocks = 0;

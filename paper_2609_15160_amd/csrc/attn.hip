@@ -42,8 +42,8 @@ template <typename F, typename P> __device__ __forceinline__ F ld_stream(const P
   }
 }
 
-// Queries per wave and waves per workgroup of the prefill attention.
-constexpr int kPreQW = 16, kPreWaves = 8;
+// Queries per wave of the prefill attention.
+constexpr int kPreQW = 16;
 
 __device__ __forceinline__ float4 scale4(float4 v, float s) { return make_float4(v.x * s, v.y * s, v.z * s, v.w * s); }
 
@@ -316,15 +316,16 @@ __global__ __launch_bounds__(W * 64) void k_attn_decode(AttnDecodeArgs a) {
   }
 }
 
-template <typename T, int D, bool SPLITQ>
-__global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill(AttnPrefillArgs a) {
+// WV: waves of a workgroup (8, or 4 where a launch has few of them).
+template <typename T, int D, bool SPLITQ, int WV>
+__global__ __launch_bounds__(WV * 64, 2) void k_attn_prefill(AttnPrefillArgs a) {
   using M = Mfma<T>;
   typedef typename M::frag Frag;
   constexpr int KS = M::KS, EPL = M::EPL;
   constexpr int QW = kPreQW;                      // queries per wave
   constexpr int QN = QW / 16;                     // query column tiles per wave
-  constexpr int NTH = kPreWaves * kWave;          // threads
-  constexpr int BQ = kPreWaves * QW;              // queries per workgroup
+  constexpr int NTH = WV * kWave;                 // threads
+  constexpr int BQ = WV * QW;                     // queries per workgroup
   constexpr int BKEY = 4 * kPage;                 // keys per tile: four pages
   constexpr int NT = BKEY / 16;                   // 16-key subtiles
   constexpr int KSTEPS = D / KS;
@@ -363,6 +364,21 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
   const int GH = a.G * c.H, u = blockIdx.x;
   const int qt = QT - 1 - u / GH, g = (u % GH) / c.H, h = u % c.H;
   const int b = a.b0 + g;
+  // A wave's 64 chunks of one load round lie in one page's K or V block (a
+  // page block holds a multiple of 64 chunks), so the page and the K/V choice
+  // are wave-uniform.  The first two tiles' table entries are read together
+  // with the cache length, clamped to the table rather than to the cache:
+  // entries past the cache may be stale or empty, and only have to be pages.
+  static_assert((KBLK / EPC) % kWave == 0, "a wave's chunks within one page block");
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  auto round_page = [&](int u) { return ((wu * kWave + u * NTH) % (CH / 2)) / (KBLK / EPC); };
+  const int32_t* pt = c.page_table + ((int64_t)b * c.R + a.loop) * c.pages_per_seq;
+  int first_pg[2][CPT];
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int u = 0; u < CPT; ++u)
+      first_pg[k][u] = min(max(pt[min(k * 4 + round_page(u), c.pages_per_seq - 1)], 0), c.max_pages - 1);
   // the call's nq queries are cache entries [n - nq, n) of (b, loop): query
   // row a (compact index n0 + a) sees keys [0, n0 + a]
   const int n = c.cache_len[b * c.R + a.loop];
@@ -371,7 +387,6 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
   const int q0 = qt * BQ;
   if (q0 >= nq) return;
   const int row0 = a.row_off[g * c.R + a.loop];  // compact row of the sequence's first query
-  const int32_t* pt = c.page_table + ((int64_t)b * c.R + a.loop) * c.pages_per_seq;
   const T* pool = reinterpret_cast<const T*>(c.pool);
   const int64_t koff = k_block(c, a.layer, h), voff = v_block(c, a.layer, h);
   const int npages = (n + kPage - 1) / kPage;
@@ -413,20 +428,12 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
   }
 
   // one K + V tile: chunk ci < CH/2 is K chunk ci, else V chunk ci - CH/2;
-  // pages past the cache are stored as zeros (their scores are masked).  A
-  // page block holds a multiple of 64 chunks, so the 64 chunks of one wave
-  // in round u lie in one block: its page and K/V choice are wave-uniform.
-  // The tile's table entries are read first (scalar loads), then every data
-  // load is issued, from the last page where the tile runs past the cache,
-  // so that none waits on another.
-  static_assert((KBLK / EPC) % kWave == 0, "a wave's chunks within one page block");
-  const int wu = __builtin_amdgcn_readfirstlane(w);
-  auto round_page = [&](int u) { return ((wu * kWave + u * NTH) % (CH / 2)) / (KBLK / EPC); };
+  // pages past the cache are stored as zeros (their scores are masked).  The
+  // tile's table entries are read first (scalar loads), then every data load
+  // is issued, from the last page where the tile runs past the cache, so that
+  // none waits on another.
   uint4 pa[CPT], pb[CPT];  // tiles in flight in registers
-  auto load_tile = [&](int kt, uint4 (&pre)[CPT]) __attribute__((always_inline)) {
-    int pg[CPT];
-#pragma unroll
-    for (int u = 0; u < CPT; ++u) pg[u] = pt[min(kt * 4 + round_page(u), npages - 1)];
+  auto load_pages = [&](const int (&pg)[CPT], uint4 (&pre)[CPT]) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < CPT; ++u) {
       const int ci0 = wu * kWave + u * NTH;  // the wave's first chunk of round u
@@ -434,6 +441,12 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
       const int off = ((ci0 % (CH / 2)) % (KBLK / EPC) + lane) * EPC;
       pre[u] = *reinterpret_cast<const uint4*>(pool + (int64_t)pg[u] * c.page_elems + (kv ? voff : koff) + off);
     }
+  };
+  // (the table entries of a tile are read while the tile before last of its
+  // registers is in use, two tiles ahead of its data loads)
+  auto read_pages = [&](int kt, int (&pg)[CPT]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) pg[u] = pt[min(kt * 4 + round_page(u), npages - 1)];
   };
   auto store_tile = [&](int kt, int buf, const uint4 (&pre)[CPT]) __attribute__((always_inline)) {
 #pragma unroll
@@ -609,28 +622,37 @@ __global__ __launch_bounds__(kPreWaves * 64, 16 / kPreWaves) void k_attn_prefill
     // Loads past the last tile reread its pages (clamped) and are never
     // skipped, so the wait before a store counts exactly the one tile issued
     // after it.
-    load_tile(0, pa);
-    load_tile(1, pb);
+    int ga[CPT], gb[CPT];  // pages of the next tiles of pa and pb
+    load_pages(first_pg[0], pa);
+    load_pages(first_pg[1], pb);
+    read_pages(2, ga);
+    read_pages(3, gb);
     store_tile(0, 0, pa);
     __syncthreads();
     for (int kt = 0; kt < nkt; kt += 2) {
-      load_tile(kt + 2, pa);
+      load_pages(ga, pa);
+      read_pages(kt + 4, ga);
       use_tile(kt, 0);
       if (kt + 1 < nkt) store_tile(kt + 1, 1, pb);
       __syncthreads();
       if (kt + 1 < nkt) {
-        load_tile(kt + 3, pb);
+        load_pages(gb, pb);
+        read_pages(kt + 5, gb);
         use_tile(kt + 1, 1);
         if (kt + 2 < nkt) store_tile(kt + 2, 0, pa);
         __syncthreads();
       }
     }
   } else {  // float32: one tile ahead (two would spill at D = 128)
-    load_tile(0, pa);
+    load_pages(first_pg[0], pa);
     store_tile(0, 0, pa);
     __syncthreads();
     for (int kt = 0; kt < nkt; ++kt) {
-      if (kt + 1 < nkt) load_tile(kt + 1, pa);
+      if (kt + 1 < nkt) {
+        int pg[CPT];
+        read_pages(kt + 1, pg);
+        load_pages(pg, pa);
+      }
       use_tile(kt, kt & 1);
       if (kt + 1 < nkt) store_tile(kt + 1, (kt & 1) ^ 1, pa);
       __syncthreads();
@@ -703,32 +725,35 @@ hipError_t attn_decode_blocks_per_cu(int D, int waves, int* blocks) {
   }
 }
 
+// Workgroups of 8 waves share each staged key tile among 128 queries; with
+// fewer than two of them per compute unit, workgroups of 4 waves spread the
+// same waves over more compute units.  Measured (12 x 64 heads, loop 1, us with
+// 8 and 4 waves): 1 x 1000 tokens 22.1 and 20.4, 3 x 777 20.5 and
+// 20.1, the later loops of both 5 to 12% less with 4.
+template <typename T, int D, bool SPLITQ>
+hipError_t launch_prefill_d(const AttnPrefillArgs& a, hipStream_t s) {
+  auto blocks = [&](int waves) { return (int64_t)a.G * ((a.T + waves * kPreQW - 1) / (waves * kPreQW)) * a.c.H; };
+  if (blocks(8) < 2 * (int64_t)a.cus)
+    hipLaunchKernelGGL((k_attn_prefill<T, D, SPLITQ, 4>), dim3((unsigned)blocks(4)), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_attn_prefill<T, D, SPLITQ, 8>), dim3((unsigned)blocks(8)), dim3(512), 0, s, a);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_attn_prefill(const AttnPrefillArgs& a, hipStream_t s) {
-  const int BQ = kPreWaves * kPreQW;
-  const int QT = (a.T + BQ - 1) / BQ;
-  const dim3 grid(a.G * QT * a.c.H), block(kPreWaves * kWave);
   if (a.G <= 0) return hipSuccess;
+  // a 16-wide head needs the 4-deep f32 MFMA; bf16 models reject head_dim 16
   switch (a.c.D) {
     case 16:
-      // a 16-wide head needs the 4-deep f32 MFMA; bf16 models reject head_dim 16
-      if constexpr (sizeof(T) == 4) {
-        hipLaunchKernelGGL((k_attn_prefill<T, 16, true>), grid, block, 0, s, a);
-        break;
-      } else {
-        return hipErrorInvalidValue;
-      }
+      if constexpr (sizeof(T) == 4) return launch_prefill_d<T, 16, true>(a, s);
+      return hipErrorInvalidValue;
     case 64:
-      if (sizeof(T) == 2 && a.q16) hipLaunchKernelGGL((k_attn_prefill<T, 64, false>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((k_attn_prefill<T, 64, true>), grid, block, 0, s, a);
-      break;
+      return sizeof(T) == 2 && a.q16 ? launch_prefill_d<T, 64, false>(a, s) : launch_prefill_d<T, 64, true>(a, s);
     case 128:
-      if (sizeof(T) == 2 && a.q16) hipLaunchKernelGGL((k_attn_prefill<T, 128, false>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((k_attn_prefill<T, 128, true>), grid, block, 0, s, a);
-      break;
+      return sizeof(T) == 2 && a.q16 ? launch_prefill_d<T, 128, false>(a, s) : launch_prefill_d<T, 128, true>(a, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template hipError_t attn_decode_blocks_per_cu<float>(int, int, int*);

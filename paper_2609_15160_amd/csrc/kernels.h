@@ -301,6 +301,7 @@ struct AttnPrefillArgs {
   float* o = nullptr;       // [rows][d], or
   bf16* o16 = nullptr;      // o as operand rows of o_parts bf16 parts
   int o_parts = 1;
+  int cus = 1;              // compute units (chooses the workgroup's waves)
   float scale_log2 = 0.f;
   const bf16* q16 = nullptr;  // bf16 keys: [rows][d] q already scaled and rounded (bf16(q * scale_log2)),
                               // read in place of q as one bf16 part (not hi + lo)

@@ -450,12 +450,13 @@ def test_bf16_prefill_single_part_activations_d768():
 
 
 @pytest.mark.parametrize("act16", [False, True], ids=["two-parts", "one-part"])
-@pytest.mark.parametrize("batch,prompt_len", [(1, 65), (2, 33), (3, 43), (5, 26), (2, 256), (9, 151)])
+@pytest.mark.parametrize("batch,prompt_len", [(1, 65), (2, 33), (3, 43), (5, 26), (2, 256), (9, 151), (40, 200)])
 def test_bf16_prefill_row_tile_edges(batch, prompt_len, act16):
     """Compact rows of the prefill projections around the tile edges (65, 66,
-    129, 130, 512 and 1359 rows in the first loop, ragged counts in the later
-    ones, sequences that share a tile), a vocabulary that fits no tile and a
-    one-tile model width: every position's logits and two decode steps against
+    129, 130, 512, 1359 and 8000 rows in the first loop, ragged counts in the
+    later ones, sequences that share a tile; four and, for the last, two key
+    groups in the attention), a vocabulary that fits no tile and a one-tile
+    model width: every position's logits and two decode steps against
     the oracle, every cache index."""
     m = synth.ModelConfig("bf16-d128", "bf16", vocab=509, d_model=128, n_heads=2, head_dim=64, d_ff=384,
                           n_layers=2, max_loops=5, batch=batch, prompt_len=prompt_len, steps=2,
@@ -466,6 +467,18 @@ def test_bf16_prefill_row_tile_edges(batch, prompt_len, act16):
     g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, all_logits=True, prefill_act_bf16=act16)
     o = parity.run_oracle(m, w, prompts, g.step_tokens, all_logits=True)
     _check_bf16(m, w, prompts, g, o, sample, f"bf16-row-tiles-{batch}x{prompt_len}-{act16}")
+
+
+@pytest.mark.parametrize("prompt_len", [60, 230, 700])
+def test_bf16_prefill_single_sequence_keeps_two_parts(prompt_len):
+    """A single sequence of at most 2048 tokens takes two bf16 parts per
+    activation with prefill_act_bf16 as without: the same bits."""
+    m = synth.CONFIGS["bf16_d768_b32x512"].replace(batch=1, prompt_len=prompt_len, steps=1)
+    w = synth.make_weights(m)
+    prompts = synth.make_prompts(m)
+    a, b = (parity.run_gpu(m, w, prompts, 1, max_pos=m.max_pos, prefill_act_bf16=x) for x in (False, True))
+    assert np.array_equal(a.prefill_logits, b.prefill_logits)
+    assert np.array_equal(a.step_logits[0], b.step_logits[0])
 
 
 def test_bf16_prefill_single_part_ragged_wide_tiles():
