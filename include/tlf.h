@@ -317,7 +317,7 @@ const char* tlf_status_str(int status);
  * d a multiple of 4).  Token t takes part in loop i exactly when its depth
  * m_t >= i.  Backward passes reuse the same calls: the gradient of the
  * gather is an in-place tlf_gs_scatter of the compact gradient into the row
- * gradients, and the gradient of the scatter is the incoming gradient itself
+ * gradients (tlf_gs_expand where there are none yet), and the gradient of the scatter is the incoming gradient itself
  * for the previous state plus its tlf_gs_gather for the block output.
  * Argument errors return TLF_E_INVALID_ARG before anything is enqueued; a
  * failed launch returns TLF_E_HIP.  Indices and slots are trusted: they must
@@ -387,6 +387,11 @@ int tlf_gs_gather(const float* d_h, const int32_t* d_index, const int32_t* d_cou
  * otherwise the two must not overlap, and d_y must overlap neither. */
 int tlf_gs_scatter(const float* d_h_prev, const float* d_y, const int32_t* d_slot, int32_t rows, int32_t d,
                    float* d_h_out, void* d_stream);
+
+/* d_out[r] = d_y[d_slot[r]] where d_slot[r] >= 0, else zeros; `rows` rows of
+ * d floats: a scatter into a zeroed tensor, without reading one.  d_out must
+ * not overlap d_y. */
+int tlf_gs_expand(const float* d_y, const int32_t* d_slot, int32_t rows, int32_t d, float* d_out, void* d_stream);
 
 /* Straight-through estimator of the depth (Appendix B), elementwise over n
  * tokens.  Forward value: d_value[t] = (float)d_depth[t].  Backward: with

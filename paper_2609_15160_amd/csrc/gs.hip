@@ -277,6 +277,38 @@ __global__ __launch_bounds__(kCopyThreads) void k_gs_scatter(const float4* prev,
   }
 }
 
+// The gather's backward: out[r] = y[slot[r]] where slot[r] >= 0, else zeros.
+// Bound by HBM: every row is written once and the active rows of y are read
+// once, where a zeroed tensor and an in-place scatter into it moved the
+// active rows twice more (a write of the zeros, then their read).
+// y + 0 keeps that form's sign of zero (+0 for a gradient of -0).
+// Backward of 8 x 4096 tokens, d = 1024, 8 loops with the forward: 1998 -> 1907 us a training pass.
+__global__ __launch_bounds__(kCopyThreads) void k_gs_expand(const float4* __restrict__ y,
+                                                            const int32_t* __restrict__ slot, int32_t rows,
+                                                            int32_t d4, float4* __restrict__ out) {
+  const int64_t limit = (int64_t)rows * d4;
+  const int64_t e0 = (int64_t)blockIdx.x * (kCopyThreads * kCopyUnroll) + threadIdx.x;
+  if (e0 >= limit) return;
+  int s[kCopyUnroll], col[kCopyUnroll];
+#pragma unroll
+  for (int u = 0; u < kCopyUnroll; ++u) {
+    const int64_t e = min(e0 + u * kCopyThreads, limit - 1);
+    const int r = (int)(e / d4);
+    col[u] = (int)(e - (int64_t)r * d4);
+    s[u] = slot[r];
+  }
+  float4 v[kCopyUnroll];
+#pragma unroll
+  for (int u = 0; u < kCopyUnroll; ++u) {
+    v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (s[u] >= 0) v[u] = y[(int64_t)s[u] * d4 + col[u]];
+  }
+#pragma unroll
+  for (int u = 0; u < kCopyUnroll; ++u)
+    if (e0 + u * kCopyThreads < limit)
+      out[e0 + u * kCopyThreads] = make_float4(v[u].x + 0.f, v[u].y + 0.f, v[u].z + 0.f, v[u].w + 0.f);
+}
+
 __global__ __launch_bounds__(kCopyThreads) void k_ste(const int32_t* __restrict__ depth,
                                                       const float* __restrict__ score,
                                                       const float* __restrict__ grad_value, int32_t n,
@@ -383,6 +415,17 @@ int tlf_gs_scatter(const float* d_h_prev, const float* d_y, const int32_t* d_slo
   else
     hipLaunchKernelGGL(k_gs_scatter<false>, dim3(copy_blocks(e4)), dim3(kCopyThreads), 0, (hipStream_t)stream,
                        (const float4*)d_h_prev, (const float4*)d_y, d_slot, rows, d / 4, (float4*)d_h_out);
+  return launch_status();
+}
+
+int tlf_gs_expand(const float* d_y, const int32_t* d_slot, int32_t rows, int32_t d, float* d_out, void* stream) {
+  if (rows < 0 || d <= 0 || d % 4 != 0) return TLF_E_INVALID_ARG;
+  if (rows == 0) return TLF_OK;
+  if (!d_y || !d_slot || !d_out || !aligned16(d_y) || !aligned16(d_out)) return TLF_E_INVALID_ARG;
+  const int64_t e4 = (int64_t)rows * (d / 4);
+  if (copy_blocks(e4) > INT32_MAX / 2) return TLF_E_INVALID_ARG;
+  hipLaunchKernelGGL(k_gs_expand, dim3(copy_blocks(e4)), dim3(kCopyThreads), 0, (hipStream_t)stream,
+                     (const float4*)d_y, d_slot, rows, d / 4, (float4*)d_out);
   return launch_status();
 }
 

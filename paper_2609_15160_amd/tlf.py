@@ -94,7 +94,7 @@ class CacheStats(ctypes.Structure):
 
 EXPORTS = ("tlf_init", "tlf_prefill", "tlf_decode_step", "tlf_cache_stats", "tlf_set_profiling", "tlf_destroy",
            "tlf_status_str", "tlf_gs_plan", "tlf_gs_plan_ws", "tlf_gs_plan_noalloc", "tlf_gs_gather",
-           "tlf_gs_scatter", "tlf_ste", "tlf_probe_read")
+           "tlf_gs_scatter", "tlf_gs_expand", "tlf_ste", "tlf_probe_read")
 
 PROBE_READ_GRAIN = 32768
 
@@ -159,6 +159,8 @@ def load(path: str = LIB_PATH):
     lib.tlf_gs_gather.restype = ctypes.c_int
     lib.tlf_gs_scatter.argtypes = [vp, vp, vp, i32, i32, vp, vp]
     lib.tlf_gs_scatter.restype = ctypes.c_int
+    lib.tlf_gs_expand.argtypes = [vp, vp, i32, i32, vp, vp]
+    lib.tlf_gs_expand.restype = ctypes.c_int
     lib.tlf_ste.argtypes = [vp, vp, vp, i32, vp, vp, vp]
     lib.tlf_ste.restype = ctypes.c_int
     _lib = lib

@@ -110,6 +110,18 @@ def scatter_raw(h_prev: torch.Tensor, y: torch.Tensor, p: LoopPlan, out: torch.T
     return out
 
 
+def expand_raw(y: torch.Tensor, p: LoopPlan) -> torch.Tensor:
+    """The compact rows `y` at their rows of a new [rows, d] tensor, zeros elsewhere (the gather's gradient)."""
+    _rows_tensor(y, "y")
+    if y.shape[0] != p.count:
+        raise ValueError(f"expand: y {tuple(y.shape)}, plan rows {p.rows} count {p.count}")
+    out = torch.empty((p.rows, y.shape[1]), dtype=y.dtype, device=y.device)
+    # with no active row y is empty (no address) and never read: pass out's
+    yp = _ptr(y) if y.numel() else _ptr(out)
+    _check(tlf.load().tlf_gs_expand(yp, _ptr(p.slot), p.rows, y.shape[1], _ptr(out), _stream()), "tlf_gs_expand")
+    return out
+
+
 class _Gather(torch.autograd.Function):
     @staticmethod
     def forward(ctx, h, p):
@@ -119,9 +131,9 @@ class _Gather(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, g):
-        dh = torch.zeros(ctx.shape, dtype=g.dtype, device=g.device)
-        scatter_raw(dh, g.contiguous(), ctx.p, out=dh)
-        return dh, None
+        if ctx.shape[0] != ctx.p.rows:
+            raise ValueError(f"gather: h {tuple(ctx.shape)}, plan rows {ctx.p.rows} count {ctx.p.count}")
+        return expand_raw(g.contiguous(), ctx.p), None
 
 
 class _Scatter(torch.autograd.Function):

@@ -255,6 +255,10 @@ def test_gather_scatter_argument_errors_need_no_device():
     assert lib.tlf_gs_scatter(dummy, dummy, dummy, 8, 0, dummy, None) == bad
     assert lib.tlf_gs_scatter(dummy, None, dummy, 8, 8, dummy, None) == bad
     assert lib.tlf_gs_scatter(dummy, dummy, dummy, 0, 8, dummy, None) == tlf.OK
+    assert lib.tlf_gs_expand(dummy, dummy, 8, 6, dummy, None) == bad             # d % 4
+    assert lib.tlf_gs_expand(None, dummy, 8, 8, dummy, None) == bad
+    assert lib.tlf_gs_expand(dummy, dummy, 8, 8, ctypes.c_void_p(20), None) == bad  # alignment
+    assert lib.tlf_gs_expand(dummy, dummy, 0, 8, dummy, None) == tlf.OK
     assert lib.tlf_ste(dummy, dummy, dummy, -1, dummy, dummy, None) == bad
     assert lib.tlf_ste(None, dummy, dummy, 4, dummy, None, None) == bad
     assert lib.tlf_ste(dummy, None, dummy, 4, None, dummy, None) == bad

@@ -143,6 +143,28 @@ def test_gather_scatter_parity(batch, seq_len, d):
         assert np.allclose(out, want, rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("batch,seq_len,d", [(1, 1, 4), (3, 17, 8), (2, 333, 260), (1, 4099, 1024)])
+def test_gather_gradient_is_a_scatter_into_zeros(batch, seq_len, d):
+    """The gather's gradient bit for bit (the sign of zeros, infinities and NaN
+    among the values), loops with every row and with none."""
+    train = _train()
+    rows = batch * seq_len
+    m = synth.make_train_depths(rows, 8, seed=rows + d)
+    h = _dev(synth.make_train_states(rows, d, seed=d)).requires_grad_(True)
+    for i in (0, 2, 8, 9):
+        p = train.plan(_dev(m), batch, seq_len, i)
+        g = synth.make_train_states(p.count, d, seed=i, stream=104)
+        flat = g.reshape(-1)
+        special = np.array([-0.0, 0.0, np.inf, -np.inf, np.nan], np.float32)[: flat.size]
+        flat[: special.size] = special
+        want = torch.zeros(rows, d, device="cuda")
+        train.scatter_raw(want, _dev(g), p, out=want)
+        got, = torch.autograd.grad(train.gather(h, p), h, _dev(g))
+        nan = torch.isnan(want)
+        assert torch.equal(torch.isnan(got), nan)
+        assert torch.equal(got[~nan].view(torch.int32), want[~nan].view(torch.int32))
+
+
 def test_full_size_training_batch():
     """Batch 8 x 4096 tokens, d = 1024 (the prefill workload's shape), every
     loop: plan bit-exact, sampled gathered rows bit-exact, sampled scattered
