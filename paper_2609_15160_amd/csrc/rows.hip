@@ -12,6 +12,9 @@ namespace tlf {
 namespace {
 
 constexpr int kRowChunks = 16;  // 16 x 256 elements: rows up to 4096 wide
+// Embeddings of at most this many rows take a workgroup per row: as many as
+// are resident at once, so that no row waits for another's round trips.
+constexpr int kEmbedWgRows = 1024;
 constexpr int kNormChunks = 4;  // 4 x 1024 elements: rows up to 4096 wide (RMSNorm, a workgroup per row)
 
 template <int CTRL>
@@ -186,6 +189,93 @@ __global__ __launch_bounds__(256) void k_embed_route(EmbedArgs a) {
   if (a.out_margin) a.out_margin[row] = margin;
 }
 
+// The same for few rows, a workgroup of four waves per row; thread t holds
+// elements 4t + 1024c.  Latency bounds these launches (a decode step's batch,
+// a short prompt): one wave's share of W_r is 8 NC vectors, more than it
+// keeps in flight, so the kernel above makes a chain of round trips that
+// grows with the width.  Here every thread issues its whole share of W_r
+// before the token is known, so a row takes the token's round trip and its
+// embeddings'.  RL: loops covered (8 or kMaxLoops); rows of W_r past R repeat
+// row 0.
+// Measured: 64 rows of 2048 elements 35.0 -> 6.1 us, one of 768 8.6 -> 5.1.
+template <typename T, int NC, int RL>
+__global__ __launch_bounds__(256) void k_embed_route_wg(EmbedArgs a) {
+  __shared__ float s_part[4][RL + 1];
+  const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
+  const int row = blockIdx.x;
+  int tok = a.tokens[row];
+  const int sl = (a.prefill_T > 0 ? a.tokens : a.seq_len)[row];
+  float4 w[RL][NC];
+  if (a.route) {
+#pragma unroll
+    for (int i = 0; i < RL; ++i)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        w[i][c] = V4<float>::load(a.Wr + (int64_t)(i < a.R ? i : 0) * a.d + clamp_k(4 * tid + 1024 * c, a.d));
+  }
+  if (tok < 0 || tok >= a.V) {
+    if (tid == 0) set_err(a.err, kErrBadToken);
+    tok = 0;
+  }
+  const int pos = a.prefill_T > 0 ? a.pos0 + row % a.prefill_T : sl;
+  const T* e = reinterpret_cast<const T*>(a.tok_emb) + (int64_t)tok * a.d;
+  const T* p = reinterpret_cast<const T*>(a.pos_emb) + (int64_t)pos * a.d;
+  float4 h[NC];
+  float ss = 0.f;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int k = 4 * tid + 1024 * c, kk = clamp_k(k, a.d);
+    const float4 ev = V4<T>::load(e + kk), pv = V4<T>::load(p + kk);
+    h[c] = scale4(make_float4(ev.x + pv.x, ev.y + pv.y, ev.z + pv.z, ev.w + pv.w), k < a.d ? 1.f : 0.f);
+    ss = sumsq(h[c], ss);
+  }
+  ss = wave_sum(ss);
+  if (lane == 0) s_part[wv][RL] = ss;
+  if (a.route) {
+    float z[RL];
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+      z[i] = 0.f;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        z[i] = fmaf(w[i][c].w, h[c].w, fmaf(w[i][c].z, h[c].z, fmaf(w[i][c].y, h[c].y, fmaf(w[i][c].x, h[c].x, z[i]))));
+    }
+#pragma unroll
+    for (int i = 0; i < RL; ++i) z[i] = wave_sum(z[i]);
+    if (lane == 0)
+#pragma unroll
+      for (int i = 0; i < RL; ++i) s_part[wv][i] = z[i];
+  }
+  __syncthreads();
+  auto total = [&](int i) { return (s_part[0][i] + s_part[1][i]) + (s_part[2][i] + s_part[3][i]); };
+  ss = total(RL);
+  const float inv = rsqrtf(ss / (float)a.d + a.eps);
+  if (a.ssq)
+    for (int k = tid; k < a.d / 32; k += 256) a.ssq[(int64_t)row * (a.d / 32) + k] = k == 0 ? ss : 0.f;
+  bf16* o16 = a.x16 ? a.x16 : a.y16;
+  const float sc16 = a.x16 ? 1.f : inv;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int k = 4 * tid + 1024 * c;
+    if (k >= a.d) continue;
+    V4<float>::store(a.x + (int64_t)row * a.d + k, h[c]);
+    if (a.y) V4<float>::store(a.y + (int64_t)row * a.d + k, scale4(h[c], inv));
+    if (!o16) continue;
+    if (a.parts == 2) store_operand4<2>(o16, row, k, a.d, scale4(h[c], sc16));
+    else store_operand4<1>(o16, row, k, a.d, scale4(h[c], sc16));
+  }
+  if (!a.route || tid != 0) return;
+  float z[kMaxLoops];
+#pragma unroll
+  for (int i = 0; i < kMaxLoops; ++i) z[i] = i < RL && i < a.R ? total(i) + a.br[i] : 0.f;
+  int m;
+  float margin;
+  decide_depth(z, a.R, a.rule, a.threshold, a.fixed, &m, &margin);
+  a.depth[row] = m;
+  if (a.out_depth) a.out_depth[row] = m;
+  if (a.out_margin) a.out_margin[row] = margin;
+}
+
 // ---------------------------------------------------------------------------
 // Output layer of the MLP router on hidden rows (z = W_r h + b_r), then the
 // depth rule.  One wave per row; lane l holds elements 4l + 256c.
@@ -304,6 +394,19 @@ __global__ __launch_bounds__(256) void k_resid_norm(ResidNormArgs a) {
 template <typename T> hipError_t launch_embed_route(const EmbedArgs& a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   if (a.d <= 0 || a.d % 4 != 0 || a.d > 256 * kRowChunks) return hipErrorInvalidValue;
+  if (a.rows <= kEmbedWgRows) {
+#define TLF_EMBED(NC)                                                                                       \
+  if (a.R <= 8) hipLaunchKernelGGL((k_embed_route_wg<T, NC, 8>), dim3(a.rows), dim3(256), 0, s, a);         \
+  else hipLaunchKernelGGL((k_embed_route_wg<T, NC, kMaxLoops>), dim3(a.rows), dim3(256), 0, s, a)
+    switch ((a.d + 1023) / 1024) {
+      case 1: TLF_EMBED(1); break;
+      case 2: TLF_EMBED(2); break;
+      case 3: TLF_EMBED(3); break;
+      default: TLF_EMBED(4); break;
+    }
+#undef TLF_EMBED
+    return hipGetLastError();
+  }
 #define TLF_EMBED(NC) hipLaunchKernelGGL((k_embed_route<T, NC>), dim3((a.rows + 3) / 4), dim3(256), 0, s, a)
   TLF_NC_SWITCH((a.d + 255) / 256, TLF_EMBED)
 #undef TLF_EMBED
