@@ -32,6 +32,8 @@ __device__ __forceinline__ void add_stat(long long* p, unsigned long long v) {
 }
 constexpr int kPlanChunks = 4;  // kPlanThreads * kPlanChunks >= max batch (NT = kPlanThreads above kPlanThreads sequences)
 
+// NCH chunks of NT sequences, RL loops at most.
+template <int NCH, int RL>
 __global__ __launch_bounds__(kPlanThreads) void k_plan_decode(DecodePlanArgs a) {
   const CacheView& c = a.c;
   const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6, B = a.B, R = c.R;
@@ -50,26 +52,28 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_decode(DecodePlanArgs a) 
   // and the allocator in one round trip, then the page-table entry of each
   // cache's partly filled last page; sequences beyond (chunks >= 1) read
   // theirs where they are used
-  int m_of[kPlanChunks], row_of[kPlanChunks];
+  int m_of[NCH], row_of[NCH];
 #pragma unroll
-  for (int ch = 0; ch < kPlanChunks; ++ch) {
+  for (int ch = 0; ch < NCH; ++ch) {
     const int b = ch * NT + tid;
     m_of[ch] = b < B ? a.depth[b] : 0;
     row_of[ch] = -1;
   }
-  int seq0, len0[kMaxLoops], page0[kMaxLoops];
+  int seq0, len0[RL], page0[RL];
   {
-    const bool in = tid < B;
-    seq0 = in ? c.seq_len[tid] : 0;
+    // clamped into range rather than guarded: a load under a lane's condition
+    // can cost a round trip of its own.  Threads past the batch read its last
+    // sequence and a loop past R the last loop; both have no depth to use it.
+    const int b = max(0, min(tid, B - 1));
+    seq0 = c.seq_len[b];
 #pragma unroll
-    for (int i = 0; i < kMaxLoops; ++i) len0[i] = in && i < R ? c.cache_len[tid * R + i] : 0;
+    for (int i = 0; i < RL; ++i) len0[i] = c.cache_len[b * R + min(i, R - 1)];
+#pragma unroll
+    for (int i = 0; i < RL; ++i)  // used where the depth runs loop i and its next slot starts no page
+      page0[i] = c.page_table[((int64_t)b * R + min(i, R - 1)) * c.pages_per_seq +
+                              min(len0[i] / kPage, c.pages_per_seq - 1)];
   }
-  const int base0 = tid == 0 ? *c.page_next : 0;
-#pragma unroll
-  for (int i = 0; i < kMaxLoops; ++i)
-    page0[i] = (i < m_of[0] && len0[i] % kPage != 0)
-                   ? c.page_table[((int64_t)tid * R + i) * c.pages_per_seq + len0[i] / kPage]
-                   : -1;
+  const int base0 = *c.page_next;
   auto len_at = [&](int ch, int b, int i) __attribute__((always_inline)) {
     return ch == 0 ? len0[i] : c.cache_len[b * R + i];
   };
@@ -77,7 +81,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_decode(DecodePlanArgs a) 
   if (tid == 0) { s_kvread = 0ull; s_base = base0; }
   __syncthreads();
 #pragma unroll
-  for (int ch = 0; ch < kPlanChunks; ++ch)
+  for (int ch = 0; ch < NCH; ++ch)
     if (m_of[ch] > 0) atomicAdd(&cnt[m_of[ch]], 1);
   __syncthreads();
   if (tid == 0) {
@@ -96,7 +100,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_decode(DecodePlanArgs a) 
   // 1. rank of b among the sequences of its depth with smaller b
   const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
-  for (int ch = 0; ch < kPlanChunks; ++ch) {
+  for (int ch = 0; ch < NCH; ++ch) {
     if (ch * NT >= B) break;  // uniform
     const int m = m_of[ch];
     int rank = 0;
@@ -126,19 +130,19 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_decode(DecodePlanArgs a) 
   // row's first new page follows from a block prefix sum (every thread
   // carries the running total, so no barrier is needed between chunks), and
   // the entries each row's attention reads
-  int ex_of[kPlanChunks];
+  int ex_of[NCH];
   int total = 0;
   unsigned long long rd_sum = 0ull;
   const int lim_all = a.dense ? top : 0;  // dense: loops every row reads
 #pragma unroll
-  for (int ch = 0; ch < kPlanChunks; ++ch) {
+  for (int ch = 0; ch < NCH; ++ch) {
     ex_of[ch] = 0;
     if (ch * NT >= B) break;  // uniform
     const int b = ch * NT + tid, m = m_of[ch];
     int need = 0;
     unsigned long long rd = 0ull;
 #pragma unroll
-    for (int i = 0; i < kMaxLoops; ++i) {
+    for (int i = 0; i < RL; ++i) {
       if (m > 0 && i < m) {
         const int len = len_at(ch, b, i);
         need += len % kPage == 0;
@@ -196,27 +200,27 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_decode(DecodePlanArgs a) 
   // each compact row's slot offset, and the row order; no barrier follows
   // these stores
 #pragma unroll
-  for (int ch = 0; ch < kPlanChunks; ++ch) {
+  for (int ch = 0; ch < NCH; ++ch) {
     if (ch * NT >= B) break;  // uniform
     const int b = ch * NT + tid, m = m_of[ch];
     if (m > 0 && !oom) {
-      int len[kMaxLoops], page[kMaxLoops];
+      int len[RL], page[RL];
       const int lim = a.dense ? top : m;  // loops whose cache this row reads
 #pragma unroll
-      for (int i = 0; i < kMaxLoops; ++i) {
+      for (int i = 0; i < RL; ++i) {
         len[i] = i < lim ? len_at(ch, b, i) : 0;
         page[i] = ch == 0 ? page0[i] : -1;
       }
       if (ch > 0) {
 #pragma unroll
-        for (int i = 0; i < kMaxLoops; ++i)
+        for (int i = 0; i < RL; ++i)
           if (i < m && len[i] % kPage != 0)
             page[i] = c.page_table[((int64_t)b * R + i) * c.pages_per_seq + len[i] / kPage];
       }
       int next = base + ex_of[ch];
       const int t = ch == 0 ? seq0 : c.seq_len[b];
 #pragma unroll
-      for (int i = 0; i < kMaxLoops; ++i) {
+      for (int i = 0; i < RL; ++i) {
         if (i < m) {
           const int slot = len[i];
           if (slot % kPage == 0) {
@@ -365,9 +369,13 @@ __global__ void k_argmax_finalize(const unsigned long long* keys, int groups, in
   const int b = blockIdx.x * (blockDim.x / kWave) + (int)(threadIdx.x / kWave), lane = lane_id();
   if (b >= B) return;
   unsigned long long key = 0ull;
-  for (int gi = lane; gi < groups; gi += kWave) {
-    const unsigned long long k = keys[(int64_t)b * groups + gi];
-    key = k > key ? k : key;
+  // eight loads in flight (a repeat of the last key changes no maximum)
+  for (int g0 = lane; g0 < groups; g0 += 8 * kWave) {
+    unsigned long long k[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) k[u] = keys[(int64_t)b * groups + min(g0 + u * kWave, groups - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) key = k[u] > key ? k[u] : key;
   }
 #pragma unroll
   for (int o = 1; o < kWave; o <<= 1) {
@@ -390,7 +398,15 @@ hipError_t launch_plan_decode(const DecodePlanArgs& a, hipStream_t s) {
   // fewer threads for a small batch: the planner's many barriers then wait
   // for fewer waves
   const int nt = std::min(kPlanThreads, std::max(kWave, (a.B + kWave - 1) / kWave * kWave));
-  hipLaunchKernelGGL(k_plan_decode, dim3(1), dim3(nt), 0, s, a);
+  // one chunk and eight loops cover most steps: one workgroup runs its code
+  // once, so the unrolled code that it does not fetch is time saved (with the
+  // clamped loads, 1 sequence 10.1 -> 7.3 us, 64 sequences 12.6 -> 8.6)
+  if (a.B > kPlanThreads)
+    hipLaunchKernelGGL((k_plan_decode<kPlanChunks, kMaxLoops>), dim3(1), dim3(nt), 0, s, a);
+  else if (a.c.R > 8)
+    hipLaunchKernelGGL((k_plan_decode<1, kMaxLoops>), dim3(1), dim3(nt), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_plan_decode<1, 8>), dim3(1), dim3(nt), 0, s, a);
   return hipGetLastError();
 }
 
