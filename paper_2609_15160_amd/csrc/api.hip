@@ -578,6 +578,7 @@ int run_decode(tlf_ctx* ctx, hipStream_t s, const int32_t* tokens, float* logits
       at.o_ks = Mfma<T>::KS; at.o_epl = Mfma<T>::EPL;
       at.scale_log2 = 1.4426950408889634f / std::sqrt((float)c.head_dim);
       at.waves = attn_waves(ctx);
+      at.rows = B;
       at.grid = ctx->cus * ctx->attn_blocks[at.waves == 4 ? 0 : 1];
       if (ctx->profile_attn) {
         TLF_HIP(ctx->begin_timed(s, true));

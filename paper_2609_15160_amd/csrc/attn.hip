@@ -20,6 +20,8 @@
 // each lane holds (no data movement between the two products); both run on
 // MFMA with an online softmax per query.  Against bf16 keys q enters as hi +
 // lo parts, or as the one bf16 part that the projection wrote (q16).
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace tlf {
@@ -95,17 +97,25 @@ __device__ __forceinline__ float merge_scale(float m, float mn) {
   return m == kNegInf ? 0.f : exp2_weight(m - mn);
 }
 
-// Sum over aligned groups of G lanes (G = 2, 4, 8, 16, 32) with DPP moves
-// inside rows of 16 lanes and a shuffle beyond them.
+// Waves per SIMD that the decode attention's registers must leave room for:
+// two at head width 128 in bf16, whose two batches in flight (8 KB of K and 8
+// KB of V per wave and batch) take 234 registers; one batch at three waves
+// (168 registers) was slower: 2685 against 2762 us for a decode step of 64
+// sequences x 4096 tokens, d = 2048.
+template <typename T, int D, int W> constexpr int decode_waves() {
+  if (D != 128) return 1;
+  return sizeof(T) == 2 ? 2 : W == 8 ? 4 : 1;
+}
+
 template <typename T, int D, int W>
-__global__ __launch_bounds__(W * 64) void k_attn_decode(AttnDecodeArgs a) {
+__global__ __launch_bounds__(W * 64, (decode_waves<T, D, W>())) void k_attn_decode(AttnDecodeArgs a) {
   using M = Mfma<T>;
   constexpr int KS = M::KS, EPL = M::EPL;
   constexpr int PPI = EPL == 8 ? 2 : 1;                    // pages per iteration (4 * PPI slots per lane)
   constexpr int KSTEPS = D / KS;                            // S MFMAs per page
   constexpr int DT = D / 16;                                // output dimension tiles
   constexpr int PVM = 4 * PPI / EPL;                        // P.V MFMAs per iteration
-  constexpr int NBUF = D * (int)sizeof(T) <= 128 ? 2 : 1;   // batches in flight
+  constexpr int NBUF = D * (int)sizeof(T) <= 128 || sizeof(T) == 2 ? 2 : 1;   // batches in flight
   constexpr int NQ = EPL == 8 ? 2 : 1;                      // parts of q (hi, lo)
   static_assert(KSTEPS >= 1 && D % 16 == 0, "head_dim");
   static_assert(4 * PPI % EPL == 0, "P.V k-slots");
@@ -119,17 +129,36 @@ __global__ __launch_bounds__(W * 64) void k_attn_decode(AttnDecodeArgs a) {
   const int lane = lane_id(), w = threadIdx.x >> 6;
   const int quad = lane >> 4, c16 = lane & 15;
   const int H = c.H, R = c.R, i = a.loop;
-  const int nunits = *a.nact * H;
   const T* pool = reinterpret_cast<const T*>(c.pool);
 
-  for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
+  // A unit's sequence, cache length and first W x 64 page-table entries, the
+  // entries read together with the length (they do not depend on it).  The
+  // first unit's go out together with the active count: the row order holds
+  // all a.rows sequences and the grid has at most a.rows x H workgroups.
+  int u = blockIdx.x, L = 0, p_first = 0;
+  const int32_t* pt = nullptr;
+  auto unit_start = [&]() __attribute__((always_inline)) {
+    const int64_t bi = (int64_t)a.perm[u / H] * R + i;
+    pt = c.page_table + bi * c.pages_per_seq;
+    p_first = pt[min((int)threadIdx.x, c.pages_per_seq - 1)];
+    L = c.cache_len[bi];
+  };
+  unit_start();
+  const int nunits = *a.nact * H;
+
+  while (u < nunits) {
     const int k = u / H, h = u % H;
-    const int b = a.perm[k];
-    // the row's first W x 64 page-table entries are read together with the
-    // cache length (they do not depend on it), the rest once it is known
-    const int32_t* pt = c.page_table + ((int64_t)b * R + i) * c.pages_per_seq;
-    const int p_first = threadIdx.x < c.pages_per_seq ? pt[threadIdx.x] : 0;
-    const int L = c.cache_len[b * R + i];
+    // q (float32) as the B operand of S = K q^T, the same in all 16 columns;
+    // against bf16 keys it is split into hi and lo parts, one product each
+    KFrag qf[NQ][KSTEPS];
+    {
+      const float* qp = a.q + (int64_t)k * a.d + h * D + quad * EPL;
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) {
+        if constexpr (NQ == 2) split_frag(qp + ks * KS, qf[0][ks], qf[NQ - 1][ks]);
+        else qf[0][ks] = qp[ks * KS];
+      }
+    }
     const int np = (L + kPage - 1) / kPage;
     __syncthreads();  // the previous unit is done with s_pages and s_red
     if ((int)threadIdx.x < np) s_pages[threadIdx.x] = p_first;
@@ -142,17 +171,6 @@ __global__ __launch_bounds__(W * 64) void k_attn_decode(AttnDecodeArgs a) {
     const int64_t koff = k_block(c, a.layer, h) + (int64_t)(quad * kPage + c16) * EPL;  // fragment order
     const int64_t voff = v_block(c, a.layer, h) + (int64_t)(quad * D + c16) * 4;  // slots 4 quad .. + 3 of dim c16
 
-    // q (float32) as the B operand of S = K q^T, the same in all 16 columns;
-    // against bf16 keys it is split into hi and lo parts, one product each
-    KFrag qf[NQ][KSTEPS];
-    {
-      const float* qp = a.q + (int64_t)k * a.d + h * D + quad * EPL;
-#pragma unroll
-      for (int ks = 0; ks < KSTEPS; ++ks) {
-        if constexpr (NQ == 2) split_frag(qp + ks * KS, qf[0][ks], qf[NQ - 1][ks]);
-        else qf[0][ks] = qp[ks * KS];
-      }
-    }
     f32x4 o[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -313,6 +331,8 @@ __global__ __launch_bounds__(W * 64) void k_attn_decode(AttnDecodeArgs a) {
         a.o[oi] = Ls > 0.f ? O / Ls : 0.f;
       }
     }
+    u += gridDim.x;
+    if (u < nunits) unit_start();
   }
 }
 
@@ -683,7 +703,10 @@ __global__ __launch_bounds__(WV * 64, 2) void k_attn_prefill(AttnPrefillArgs a) 
 
 template <typename T, int D>
 hipError_t launch_decode_d(const AttnDecodeArgs& a, hipStream_t s) {
-  const dim3 grid(a.grid > 0 ? a.grid : 1);
+  // no workgroup beyond the units of a loop that every row runs: four units
+  // of the tiny float32 model had 1024 workgroups (a request of 32 + 32 tokens
+  // took 2960 us, with the units' early loads 2740)
+  const dim3 grid(std::max(1, std::min(a.grid, a.rows * a.c.H)));
   switch (a.waves) {
     case 4: hipLaunchKernelGGL((k_attn_decode<T, D, 4>), grid, dim3(256), 0, s, a); break;
     case 8: hipLaunchKernelGGL((k_attn_decode<T, D, 8>), grid, dim3(512), 0, s, a); break;

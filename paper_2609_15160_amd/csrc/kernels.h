@@ -285,6 +285,7 @@ struct AttnDecodeArgs {
   float* o = nullptr;              // [rows][d], or in MFMA fragment order (o_ks > 0)
   int o_ks = 0, o_epl = 0;         // o in the fragment order of GemmArgs::a_frag with this KS, EPL
   float scale_log2 = 0.f;          // log2(e) / sqrt(D)
+  int rows = 0;                    // sequences of the step (entries of perm)
   int grid = 0;                    // persistent workgroups
   int waves = 4;                   // waves per workgroup sharing one (row, head): 4 or 8
 };
