@@ -369,13 +369,9 @@ __global__ void k_argmax_finalize(const unsigned long long* keys, int groups, in
   const int b = blockIdx.x * (blockDim.x / kWave) + (int)(threadIdx.x / kWave), lane = lane_id();
   if (b >= B) return;
   unsigned long long key = 0ull;
-  // eight loads in flight (a repeat of the last key changes no maximum)
-  for (int g0 = lane; g0 < groups; g0 += 8 * kWave) {
-    unsigned long long k[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) k[u] = keys[(int64_t)b * groups + min(g0 + u * kWave, groups - 1)];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) key = k[u] > key ? k[u] : key;
+  for (int gi = lane; gi < groups; gi += kWave) {
+    const unsigned long long k = keys[(int64_t)b * groups + gi];
+    key = k > key ? k : key;
   }
 #pragma unroll
   for (int o = 1; o < kWave; o <<= 1) {
