@@ -703,9 +703,8 @@ __global__ __launch_bounds__(WV * 64, 2) void k_attn_prefill(AttnPrefillArgs a) 
 
 template <typename T, int D>
 hipError_t launch_decode_d(const AttnDecodeArgs& a, hipStream_t s) {
-  // no workgroup beyond the units of a loop that every row runs: four units
-  // of the tiny float32 model had 1024 workgroups (a request of 32 + 32 tokens
-  // took 2960 us, with the units' early loads 2740)
+  // no workgroup beyond the units of a loop that every row runs: the four
+  // units of the tiny float32 model had 1024 workgroups
   const dim3 grid(std::max(1, std::min(a.grid, a.rows * a.c.H)));
   switch (a.waves) {
     case 4: hipLaunchKernelGGL((k_attn_decode<T, D, 4>), grid, dim3(256), 0, s, a); break;

@@ -64,7 +64,7 @@ __device__ __forceinline__ int mod_row_depth(const GemmArgs& g, int r) {
   return g.mod_depth[g.mod_by_src ? row_src(g.rm, r) : r];
 }
 
-template <typename T, int RM, int CN, int W, int KB, int AK, int EK, bool NORM, bool MOD>
+template <typename T, int RM, int CN, int W, int KB, bool RING, int AK, int EK, bool NORM, bool MOD>
 __device__ __forceinline__ void dgemm_tile(const GemmArgs& g, int act_rows, const DgemmShared& sh) {
   using M = Mfma<T>;
   typedef typename M::frag Frag;
@@ -130,16 +130,13 @@ __device__ __forceinline__ void dgemm_tile(const GemmArgs& g, int act_rows, cons
       wo[c] = wr * g.K + quad * EPL;
     }
   }
-  // the wave's K steps of batch jb (past the wave's last step the last step
+  // the wave's K step jj into slot j (past the wave's last step the last step
   // is reread; its product is skipped)
   Frag bw[KB][CN];
-  auto load_weights = [&](int jb) {
+  auto load_weights = [&](int j, int jj) __attribute__((always_inline)) {
+    const int st = min(w + W * jj, S - 1);
 #pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      const int st = min(w + W * (jb + j), S - 1);
-#pragma unroll
-      for (int c = 0; c < CN; ++c) bw[j][c] = M::load(Wb + (wo[c] + st * wstep));
-    }
+    for (int c = 0; c < CN; ++c) bw[j][c] = M::load(Wb + (wo[c] + st * wstep));
   };
   // bookkeeping of the tile's rows (lanes of quad 0 in wave 0, one row per
   // lane and row fragment; rows past the batch read its last row) and the
@@ -183,13 +180,14 @@ __device__ __forceinline__ void dgemm_tile(const GemmArgs& g, int act_rows, cons
   // its projections)
   constexpr bool kEpilogueFirst = EK == E_RESID;
   if constexpr (kEpilogueFirst) load_epilogue_values();
-  load_weights(0);
+#pragma unroll
+  for (int j = 0; j < KB; ++j) load_weights(j, j);
 
   const float* Ab = g.A;
   int ao[RM];
 #pragma unroll
   for (int i = 0; i < RM; ++i) {
-    const int r = min(r0 + i * 16 + c16, g.rm.rows - 1);
+    const int r = min(r0 + i * 16 + c16, a_rows - 1);  // rows past the active ones reread the last
     const int arow = (AK == A_SRC) ? row_src(g.rm, r) : r;
     ao[i] = g.a_frag ? ((arow >> 4) * S * kWave + quad * 16 + (arow & 15)) * EPL : arow * g.lda + quad * EPL;
   }
@@ -214,53 +212,34 @@ __device__ __forceinline__ void dgemm_tile(const GemmArgs& g, int act_rows, cons
 #pragma unroll
   for (int i = 0; i < RM; ++i) ss[i] = 0.f;
 
-  for (int jb = 0; jb < (S + W - 1) / W; jb += KB) {
-    float av[KB][RM][EPL];
-    float gv[MOD ? KB : 1][RM][EPL];
-    if (jb > 0) load_weights(jb);
-#pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      const int stj = min(w + W * (jb + j), S - 1);
-      const int k0 = stj * KS, ka = stj * (g.a_frag ? kWave * EPL : KS);
-#pragma unroll
-      for (int i = 0; i < RM; ++i) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) av[j][i][e] = 0.f;
-        if constexpr (MOD) {
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) gv[j][i][e] = 0.f;
-        }
-        if (r0 + i * 16 >= a_rows) continue;  // uniform: the fragment's rows have exited
-        if (r0 + i * 16 + c16 < a_rows) {
-          if constexpr (EPL == 8) {
-            const float4 lo = *reinterpret_cast<const float4*>(Ab + (ao[i] + ka));
-            const float4 hi = *reinterpret_cast<const float4*>(Ab + (ao[i] + ka + 4));
-            av[j][i][0] = lo.x; av[j][i][1] = lo.y; av[j][i][2] = lo.z; av[j][i][3] = lo.w;
-            av[j][i][4] = hi.x; av[j][i][5] = hi.y; av[j][i][6] = hi.z; av[j][i][7] = hi.w;
-            if constexpr (MOD) {
-              const float4 glo = *reinterpret_cast<const float4*>(g.mod_g + (go[i] + k0));
-              const float4 ghi = *reinterpret_cast<const float4*>(g.mod_g + (go[i] + k0 + 4));
-              gv[j][i][0] = glo.x; gv[j][i][1] = glo.y; gv[j][i][2] = glo.z; gv[j][i][3] = glo.w;
-              gv[j][i][4] = ghi.x; gv[j][i][5] = ghi.y; gv[j][i][6] = ghi.z; gv[j][i][7] = ghi.w;
-            }
-          } else {
-            av[j][i][0] = Ab[ao[i] + ka];
-            if constexpr (MOD) gv[j][i][0] = g.mod_g[go[i] + k0];
-          }
-        }
+  float av[KB][RM][EPL];
+  float gv[MOD ? KB : 1][RM][EPL];
+  // row fragment i of the operand rows (and of their gamma) at K step jj, into slot j
+  auto load_rows = [&](int j, int i, int jj) __attribute__((always_inline)) {
+    const int st = min(w + W * jj, S - 1);
+    const int k0 = st * KS, ka = st * (g.a_frag ? kWave * EPL : KS);
+    if constexpr (EPL == 8) {
+      const float4 lo = *reinterpret_cast<const float4*>(Ab + (ao[i] + ka));
+      const float4 hi = *reinterpret_cast<const float4*>(Ab + (ao[i] + ka + 4));
+      av[j][i][0] = lo.x; av[j][i][1] = lo.y; av[j][i][2] = lo.z; av[j][i][3] = lo.w;
+      av[j][i][4] = hi.x; av[j][i][5] = hi.y; av[j][i][6] = hi.z; av[j][i][7] = hi.w;
+      if constexpr (MOD) {
+        const float4 glo = *reinterpret_cast<const float4*>(g.mod_g + (go[i] + k0));
+        const float4 ghi = *reinterpret_cast<const float4*>(g.mod_g + (go[i] + k0 + 4));
+        gv[j][i][0] = glo.x; gv[j][i][1] = glo.y; gv[j][i][2] = glo.z; gv[j][i][3] = glo.w;
+        gv[j][i][4] = ghi.x; gv[j][i][5] = ghi.y; gv[j][i][6] = ghi.z; gv[j][i][7] = ghi.w;
       }
+    } else {
+      av[j][i][0] = Ab[ao[i] + ka];
+      if constexpr (MOD) gv[j][i][0] = g.mod_g[go[i] + k0];
     }
-    if (jb == 0) {
-      if constexpr (!kEpilogueFirst) load_epilogue_values();
-      if (g.rm.nact) nact = *g.rm.nact;
-      if (r0 >= nact) return;  // uniform: the tile's rows have all exited
-    }
+  };
+  // products of slot j, which holds the wave's K step jj
+  auto consume = [&](int j, int jj) __attribute__((always_inline)) {
+    const int k0 = (w + W * jj) * KS;
 #pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      if (jb + j >= NJ) break;  // wave-uniform
-      const int k0 = (w + W * (jb + j)) * KS;
-#pragma unroll
-      for (int i = 0; i < RM; ++i) {
+    for (int i = 0; i < RM; ++i) {
+      if constexpr (AK == A_SRC) {
         if (g.a_copy && tn == 0) {
           // the compact copy of the operand rows (first projection of a step)
           const int r = r0 + i * 16 + c16;
@@ -271,32 +250,89 @@ __device__ __forceinline__ void dgemm_tile(const GemmArgs& g, int act_rows, cons
             for (int e = 0; e < EPL; ++e) dst[e] = av[j][i][e];
           }
         }
-        if constexpr (NORM) {
+      }
+      if constexpr (NORM) {
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) ss[i] = fmaf(av[j][i][e], av[j][i][e], ss[i]);
+        for (int e = 0; e < EPL; ++e) ss[i] = fmaf(av[j][i][e], av[j][i][e], ss[i]);
+      }
+      if constexpr (MOD) {
+        // RMSNorm(x) (1 + gamma): the norm's sum of squares above takes x itself
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) av[j][i][e] *= 1.f + gv[j][i][e];
+      }
+      if constexpr (kSplit) {
+        uint2 h0, l0, h1, l1;
+        split4(make_float4(av[j][i][0], av[j][i][1], av[j][i][2], av[j][i][3]), h0, l0);
+        split4(make_float4(av[j][i][4], av[j][i][5], av[j][i][6], av[j][i][7]), h1, l1);
+        const bf16x8 ahi = __builtin_bit_cast(bf16x8, make_uint4(h0.x, h0.y, h1.x, h1.y));
+        const bf16x8 alo = __builtin_bit_cast(bf16x8, make_uint4(l0.x, l0.y, l1.x, l1.y));
+#pragma unroll
+        for (int c = 0; c < CN; ++c) {
+          acc[i][c] = M::mma(ahi, bw[j][c], acc[i][c]);
+          acc[i][c] = M::mma(alo, bw[j][c], acc[i][c]);
         }
-        if constexpr (MOD) {
-          // RMSNorm(x) (1 + gamma): the norm's sum of squares above takes x itself
+      } else {
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) av[j][i][e] *= 1.f + gv[j][i][e];
-        }
-        if constexpr (kSplit) {
-          uint2 h0, l0, h1, l1;
-          split4(make_float4(av[j][i][0], av[j][i][1], av[j][i][2], av[j][i][3]), h0, l0);
-          split4(make_float4(av[j][i][4], av[j][i][5], av[j][i][6], av[j][i][7]), h1, l1);
-          const bf16x8 ahi = __builtin_bit_cast(bf16x8, make_uint4(h0.x, h0.y, h1.x, h1.y));
-          const bf16x8 alo = __builtin_bit_cast(bf16x8, make_uint4(l0.x, l0.y, l1.x, l1.y));
-#pragma unroll
-          for (int c = 0; c < CN; ++c) {
-            acc[i][c] = M::mma(ahi, bw[j][c], acc[i][c]);
-            acc[i][c] = M::mma(alo, bw[j][c], acc[i][c]);
-          }
-        } else {
-#pragma unroll
-          for (int c = 0; c < CN; ++c) acc[i][c] = M::mma(av[j][i][0], bw[j][c], acc[i][c]);
-        }
+        for (int c = 0; c < CN; ++c) acc[i][c] = M::mma(av[j][i][0], bw[j][c], acc[i][c]);
       }
     }
+  };
+
+  // rows of the KB steps from jb on (rows past the active ones are zeros)
+  auto load_batch_rows = [&](int jb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < KB; ++j)
+#pragma unroll
+      for (int i = 0; i < RM; ++i) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) av[j][i][e] = 0.f;
+        if constexpr (MOD) {
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) gv[j][i][e] = 0.f;
+        }
+        if (r0 + i * 16 >= a_rows) continue;  // uniform: the fragment's rows have exited
+        if (r0 + i * 16 + c16 < a_rows) load_rows(j, i, jb + j);
+      }
+  };
+  load_batch_rows(0);
+  if constexpr (!kEpilogueFirst) load_epilogue_values();
+  if (g.rm.nact) nact = *g.rm.nact;
+  if (r0 >= nact) return;  // uniform: the tile's rows have all exited
+  const int NB = (S + W - 1) / W;
+  int jb = 0;
+  if constexpr (RING) {
+    // Each slot is refilled as soon as its products are issued, so the loads
+    // of a long K are one stream and not a round trip per KB steps (d = 2048,
+    // 64 rows: gate/up 19.2 -> 17.8 us, the LM head 74.9 -> 70.6).  Every
+    // refill is unconditional (rows past the active ones reread the last),
+    // which lets the waits count the loads in flight.  Steps of a batch that
+    // is not the last are all the wave's own.
+    auto refilled = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < KB; ++j) {
+        consume(j, jb + j);
+        load_weights(j, jb + KB + j);
+#pragma unroll
+        for (int i = 0; i < RM; ++i) load_rows(j, i, jb + KB + j);
+      }
+      jb += KB;
+    };
+    if (KB < NB) {
+      refilled();  // apart from the loop: the first loads went out in another order
+      while (jb + KB < NB) refilled();
+    }
+  }
+  for (;;) {
+#pragma unroll
+    for (int j = 0; j < KB; ++j) {
+      if (jb + j >= NJ) break;  // wave-uniform
+      consume(j, jb + j);
+    }
+    jb += KB;
+    if (RING || jb >= NB) break;
+#pragma unroll
+    for (int j = 0; j < KB; ++j) load_weights(j, jb + j);
+    load_batch_rows(jb);
   }
 
   if (bk_lane) {
@@ -466,17 +502,32 @@ __device__ __forceinline__ void dgemm_tile(const GemmArgs& g, int act_rows, cons
   }
 }
 
-// One kernel, two tile shapes: the wide shape when more than `wide_above`
-// rows are active (the narrow shape would need more than one workgroup per
-// compute unit), the narrow shape otherwise.  The choice is uniform over the
-// grid and made from the active-row count the tiles need anyway.
-template <int RM, int CN> struct Shape {
-  static constexpr int BM = RM * 16, BN = CN * 16;
+// One kernel, up to three tile shapes of the same rows: wide tiles when more
+// than `narrow_upto` rows are active (the narrow ones would need more than one
+// workgroup per compute unit), thin ones of half the narrow columns when at
+// most `thin_upto` are (they too fit one workgroup per compute unit), narrow
+// ones between.  The choice is uniform over the grid and made from the
+// active-row count the tiles need anyway.
+struct ShapeRule {
+  int thin_upto, narrow_upto;
 };
 
-template <typename T, int RMn, int CNn, int RMw, int CNw, int W, int KB, int AK, int EK, bool NORM, bool MOD>
-__global__ __launch_bounds__(W * 64) void k_dgemm(GemmArgs g, int wide_above) {
+// Columns of the thin shape, in fragments: projections with few column tiles
+// per row tile (QKV and gate/up of a 768-wide model: 36 and 64 narrow ones)
+// leave most of the chip idle at up to 32 rows.  Decode steps of the 768-wide
+// model, us without and with thin QKV and gate/up, then with thin O and down:
+// 1 x 512 tokens 326, 309, 299; 32 x 512 530, 493, 470 (the last with the
+// embedding's workgroup per row, about 5); 96 x 512 678, 643, 621.
+template <int EK, int CNn> constexpr int thin_cols() {
+  if ((EK == E_QKV || EK == E_SWIGLU) && CNn == 4) return 2;
+  return EK == E_RESID && CNn == 2 ? 1 : CNn;
+}
+
+template <typename T, int RMn, int CNn, int RMw, int CNw, int W, int KB, bool RING, int AK, int EK, bool NORM, bool MOD>
+__global__ __launch_bounds__(W * 64) void k_dgemm(GemmArgs g, ShapeRule rule) {
   constexpr int SLOTS = W > 8 ? 8 : W;
+  constexpr int CNt = thin_cols<EK, CNn>();
+  constexpr int KBw = RING && CNw >= 8 ? 2 : KB;  // refilled, three batches of a wide tile would spill
   constexpr int BMX = RMn > RMw ? RMn * 16 : RMw * 16;
   constexpr int REDN = SLOTS * RMn * 16 * (CNn * 16 + 1), REDW = SLOTS * RMw * 16 * (CNw * 16 + 1);
   __shared__ float red[REDN > REDW ? REDN : REDW];
@@ -489,61 +540,76 @@ __global__ __launch_bounds__(W * 64) void k_dgemm(GemmArgs g, int wide_above) {
   const DgemmShared sh{red, s_ss, s_inv, s_orow, s_kv, s_keep, s_moff};
   const int act_rows = g.spec ? g.rm.rows : min(g.rm.nact ? *g.rm.nact : g.rm.rows, g.rm.rows);
   if constexpr (RMn != RMw || CNn != CNw) {
-    if (act_rows > wide_above) {
-      dgemm_tile<T, RMw, CNw, W, KB, AK, EK, NORM, MOD>(g, act_rows, sh);
+    if (act_rows > rule.narrow_upto) {
+      dgemm_tile<T, RMw, CNw, W, KBw, RING, AK, EK, NORM, MOD>(g, act_rows, sh);
       return;
     }
   }
-  dgemm_tile<T, RMn, CNn, W, KB, AK, EK, NORM, MOD>(g, act_rows, sh);
+  if constexpr (CNt != CNn) {
+    if (act_rows <= rule.thin_upto) {
+      dgemm_tile<T, RMn, CNt, W, KB, RING, AK, EK, NORM, MOD>(g, act_rows, sh);
+      return;
+    }
+  }
+  dgemm_tile<T, RMn, CNn, W, KB, RING, AK, EK, NORM, MOD>(g, act_rows, sh);
 }
 
-template <typename T, int RMn, int CNn, int RMw, int CNw, int W, int KB, int AK, int EK, bool NORM, bool MOD>
+template <typename T, int RMn, int CNn, int RMw, int CNw, int W, int KB, bool RING, int AK, int EK, bool NORM, bool MOD>
 hipError_t launch_cfg(const GemmArgs& a, int cus, hipStream_t s) {
   constexpr int BMn = RMn * 16, BNn = CNn * 16, BMw = RMw * 16, BNw = CNw * 16;
+  constexpr int CNt = thin_cols<EK, CNn>(), BNt = CNt * 16;
   const int tn_n = (a.N + BNn - 1) / BNn, tm_n = (a.rm.rows + BMn - 1) / BMn;
   const int tn_w = (a.N + BNw - 1) / BNw, tm_w = (a.rm.rows + BMw - 1) / BMw;
+  const int tn_t = (a.N + BNt - 1) / BNt;
   if (tn_n == 0 || tm_n == 0) return hipSuccess;
+  ShapeRule rule;
   // wide above the row count at which the narrow tiles exceed one per compute unit
-  const int wide_above = (RMn == RMw && CNn == CNw) ? a.rm.rows : std::max(1, cus / tn_n) * BMn;
-  // workgroups for the larger of the two shapes' tile counts; the narrow
-  // shape never runs on more than wide_above rows.  No workgroup beyond
-  // that: a workgroup past one per compute unit waits for a free one only
-  // to find no tile, and the launch is not over until it has run
-  const int tiles = std::max(tn_n * std::min(tm_n, (wide_above + BMn - 1) / BMn), tn_w * tm_w);
+  rule.narrow_upto = (RMn == RMw && CNn == CNw) ? a.rm.rows : std::max(1, cus / tn_n) * BMn;
+  rule.thin_upto = CNt == CNn ? 0 : std::min(cus / tn_t * BMn, rule.narrow_upto);
+  // workgroups for the largest of the shapes' tile counts; no shape runs on
+  // more rows than its limit.  No workgroup beyond that: a workgroup past one
+  // per compute unit waits for a free one only to find no tile, and the
+  // launch is not over until it has run
+  const int tm_t = std::min(tm_n, (rule.thin_upto + BMn - 1) / BMn);
+  const int tiles = std::max({tn_n * std::min(tm_n, (rule.narrow_upto + BMn - 1) / BMn), tn_w * tm_w, tn_t * tm_t});
   const int grid = kXcds * ((tiles + kXcds - 1) / kXcds);
-  hipLaunchKernelGGL((k_dgemm<T, RMn, CNn, RMw, CNw, W, KB, AK, EK, NORM, MOD>), dim3(grid), dim3(W * 64), 0, s, a,
-                     wide_above);
+  hipLaunchKernelGGL((k_dgemm<T, RMn, CNn, RMw, CNw, W, KB, RING, AK, EK, NORM, MOD>), dim3(grid), dim3(W * 64), 0, s,
+                     a, rule);
   return hipGetLastError();
 }
 
-// K steps per wave in one batch of loads: all of a wave's steps when they
-// fit in KBMAX, else batches of KBMAX.
+// K steps per wave in flight: all of a wave's steps when they fit in KBMAX,
+// else KBMAX slots, refilled one by one (with the gamma operands, whose
+// refills would spill, in batches of KBMAX).
 template <typename T, int RMn, int CNn, int RMw, int CNw, int W, int KBMAX, int AK, int EK, bool NORM,
           bool MOD = false>
 hipError_t launch_w(const GemmArgs& a, int cus, hipStream_t s) {
   const int nj = (a.K / Mfma<T>::KS + W - 1) / W;
-  if (nj <= 2 || KBMAX == 2) return launch_cfg<T, RMn, CNn, RMw, CNw, W, 2, AK, EK, NORM, MOD>(a, cus, s);
-  if (nj <= 3 || KBMAX == 3)
-    return launch_cfg<T, RMn, CNn, RMw, CNw, W, (KBMAX >= 3 ? 3 : 2), AK, EK, NORM, MOD>(a, cus, s);
-  return launch_cfg<T, RMn, CNn, RMw, CNw, W, (KBMAX >= 4 ? 4 : 2), AK, EK, NORM, MOD>(a, cus, s);
+  if (nj <= 2) return launch_cfg<T, RMn, CNn, RMw, CNw, W, 2, false, AK, EK, NORM, MOD>(a, cus, s);
+  if constexpr (KBMAX >= 3) {
+    if (nj == 3) return launch_cfg<T, RMn, CNn, RMw, CNw, W, 3, false, AK, EK, NORM, MOD>(a, cus, s);
+  }
+  if constexpr (KBMAX >= 4) {
+    if (nj == 4) return launch_cfg<T, RMn, CNn, RMw, CNw, W, 4, false, AK, EK, NORM, MOD>(a, cus, s);
+  }
+  return launch_cfg<T, RMn, CNn, RMw, CNw, W, KBMAX, !MOD, AK, EK, NORM, MOD>(a, cus, s);
 }
 
 }  // namespace
 
-// Tile shapes (rows x columns, waves), measured on the projections of a
-// 256-row batch; each kernel holds a narrow shape and a wide one and picks
-// the wide one when the narrow tiles would need more than one workgroup per
-// compute unit.
-//   QKV:     32 x 64 | 32 x 80   (8 waves)
-//   gate/up: 32 x 64 | 32 x 128  (8 waves)
-//   O:       32 x 32             (8 waves)
-//   down:    16 x 32 | 16 x 48   (16 waves)  [K > 768 in bf16; else as O]
-//   LM head: 32 x 64             (8 waves)
-//   router hidden layer: 32 x 32 (8 waves)
+// Tile shapes (rows x columns, waves): thin | narrow | wide, narrow and wide
+// measured on the projections of a 256-row batch.
+//   QKV:     32 x 32 | 32 x 64 | 32 x 80   (8 waves)
+//   gate/up: 32 x 32 | 32 x 64 | 32 x 128  (8 waves)
+//   O:       32 x 16 | 32 x 32             (8 waves)
+//   down:    16 x 16 | 16 x 32 | 16 x 48   (16 waves)  [K > 768 in bf16; else as O]
+//   LM head: 32 x 64, above 32 rows 64 x 64 (8 waves)
+//   router hidden layer: 32 x 32           (8 waves)
 template <typename T>
 hipError_t launch_dgemm(const GemmArgs& a, AKind ak, EKind ek, bool norm, int cus, hipStream_t s) {
   if (a.K <= 0 || a.K % Mfma<T>::KS != 0 || a.rm.rows <= 0 || cus <= 0) return hipErrorInvalidValue;
   if (a.a_frag && (ak != A_CMP || a.a_copy)) return hipErrorInvalidValue;
+  if (a.a_copy && ak != A_SRC) return hipErrorInvalidValue;
   if (a.copy_frag && !a.a_copy) return hipErrorInvalidValue;
   if (a.out_frag && !((ek == E_SWIGLU && a.F % Mfma<T>::KS == 0) || (ek == E_RESID && !a.scatter)))
     return hipErrorInvalidValue;
@@ -565,6 +631,12 @@ hipError_t launch_dgemm(const GemmArgs& a, AKind ak, EKind ek, bool norm, int cu
   }
   if (mod) return hipErrorInvalidValue;  // the operand scale is for the normalised projections
   if (ek == E_LOGITS && norm) {
+    // above 32 rows tiles of 64: a compute unit pulls about 20 bytes per
+    // clock here, and a tile's rows are as many bytes as its weights or more
+    // (32000 x 2048 weights, 64 rows: 72.0 us with 32-row tiles, 52.8 with 64)
+    if (a.rm.rows > 32)
+      return ak == A_SRC ? launch_w<T, 4, 4, 4, 4, 8, 2, A_SRC, E_LOGITS, true>(a, cus, s)
+                         : launch_w<T, 4, 4, 4, 4, 8, 2, A_CMP, E_LOGITS, true>(a, cus, s);
     if (ak == A_SRC) return launch_w<T, 2, 4, 2, 4, 8, 3, A_SRC, E_LOGITS, true>(a, cus, s);
     return launch_w<T, 2, 4, 2, 4, 8, 3, A_CMP, E_LOGITS, true>(a, cus, s);
   }

@@ -148,6 +148,41 @@ def test_f32_batch_over_head_gemm_rows():
     _check_f32(m, w, prompts, g, o, "f32-b130")
 
 
+@pytest.mark.parametrize("batch", [1, 33, 321, 700])
+def test_f32_decode_tile_shapes(batch):
+    """Decode projections of a 256-wide model: thin tiles, narrow ones (QKV above
+    320 rows, the others above 256) and wide ones (gate/up above 512 rows), K
+    longer than the steps in flight (8 steps per wave of QKV, gate/up and
+    down), ragged last row tiles."""
+    m = _f32_small(batch=batch, prompt_len=5, steps=3, d_model=256, n_heads=4, head_dim=64, d_ff=512)
+    w = synth.make_weights(m)
+    prompts = synth.make_prompts(m)
+    sample = sorted({0, batch // 2, batch - 1})
+    g = parity.run_gpu(m, w, prompts, m.steps, keep_logits_rows=sample)
+    o = parity.run_oracle(m, w, prompts[sample], [t[sample] for t in g.step_tokens])
+    assert np.array_equal(g.prefill_depths[sample], o.prefill_depths)
+    err = _max_err(g.prefill_logits, o.prefill_logits)
+    for s in range(m.steps):
+        assert np.array_equal(g.step_depths[s][sample], o.step_depths[s]), s
+        err = max(err, _max_err(g.step_logits[s], o.step_logits[s]))
+    _check_index_matches_depths(g, m.max_loops)
+    _report(f"f32-d256-b{batch}", max_abs_logit_err=f"{err:.3g}")
+    assert err <= F32_TOL
+
+
+@pytest.mark.parametrize("kw", [dict(max_loops=12), dict(d_model=2560, n_heads=20, head_dim=128, n_layers=1)],
+                         ids=["12-loops", "d2560"])
+def test_f32_embedding_and_planner_widths(kw):
+    """More loops than eight (the router's and the planner's wide form), and
+    rows of more than two elements quadruples per thread of the embedding."""
+    m = _f32_small(prompt_len=21, steps=6, **kw)
+    w = synth.make_weights(m)
+    prompts = synth.make_prompts(m)
+    g = parity.run_gpu(m, w, prompts, m.steps)
+    o = parity.run_oracle(m, w, prompts, g.step_tokens)
+    _check_f32(m, w, prompts, g, o, "f32-" + "-".join(kw))
+
+
 def test_f32_batch_over_planner_threads():
     """1100 sequences: the decode planner's second chunk of sequences (past
     its 1024 threads) reads its cache lengths and page-table entries where it
@@ -506,6 +541,21 @@ def test_bf16_d2048_heads_of_128_small_batch():
     g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, keep_logits_rows=sample)
     o = parity.run_oracle(m, w, prompts[sample], [t[sample] for t in g.step_tokens])
     _check_bf16(m, w, prompts, g, o, sample, "bf16_d2048-small")
+
+
+@pytest.mark.parametrize("name,batch", [("bf16_d768_b32x512", 97), ("bf16_d768_b32x512", 161),
+                                        ("bf16_d1024_prefill_b8x4096", 40), ("bf16_d2048_b64x4096", 33)])
+def test_bf16_decode_tile_shapes(name, batch):
+    """Decode projections at row counts between and past the limits of the thin
+    tiles; K of 4 (d = 1024) and 8 and 11 (d = 2048) steps per wave, refilled."""
+    full = synth.CONFIGS[name]
+    m = full.replace(batch=batch, prompt_len=18, steps=3)
+    w = synth.make_weights(full)
+    prompts = synth.make_prompts(m)
+    sample = [0, batch - 1]
+    g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, keep_logits_rows=sample)
+    o = parity.run_oracle(m, w, prompts[sample], [t[sample] for t in g.step_tokens])
+    _check_bf16(m, w, prompts, g, o, sample, f"{name}-b{batch}")
 
 
 @pytest.mark.slow
