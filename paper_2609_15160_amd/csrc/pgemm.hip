@@ -44,7 +44,7 @@ __device__ __forceinline__ void transpose4(float& v0, float& v1, float& v2, floa
 }
 
 __device__ __forceinline__ unsigned lds_addr(const void* p) {
-  return (unsigned)(uintptr_t)(__attribute__((addreinv_space(3))) const void*)p;
+  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
 // 16 bytes per lane from global memory into 64 consecutive 16-byte LDS chunks
