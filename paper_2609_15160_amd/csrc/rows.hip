@@ -12,9 +12,6 @@ namespace tlf {
 namespace {
 
 constexpr int kRowChunks = 16;  // 16 x 256 elements: rows up to 4096 wide
-// Embeddings of at most this many rows take a workgroup per row: as many as
-// are resident at once, so that no row waits for another's round trips.
-constexpr int kEmbedWgRows = 1024;
 constexpr int kNormChunks = 4;  // 4 x 1024 elements: rows up to 4096 wide (RMSNorm, a workgroup per row)
 
 template <int CTRL>
@@ -94,7 +91,7 @@ __device__ void decide_depth(const float* z, int R, int rule, float threshold, i
   *margin_out = margin;
 }
 
-// Row kernels take the number of 256-element chunks of a row (NC) as a
+// Row kernels take the number of chunks of a row (NC) as a
 // template argument and load every chunk unconditionally, the element index
 // clamped into the row (the tail's surplus lanes read the row's last four
 // elements, finite values, and multiply them by zero: a select would let the
@@ -105,101 +102,20 @@ __device__ __forceinline__ int clamp_k(int k, int n) { return k < n ? k : n - 4;
 // ---------------------------------------------------------------------------
 // h0 = E[x] + P[pos] (learned absolute position added once, Section 3.2),
 // z = W_r h0 + b_r (Eq. 2's router as a linear map), the depth rule, and
-// y = RMSNorm(h0) for the first projection.  One wave per row; lane l holds
-// elements 4l + 256c.
+// y = RMSNorm(h0) for the first projection.  A workgroup of four waves per
+// row; thread t holds elements 4t + 1024c.  Latency bounds few rows (a decode
+// step's batch): one wave's share of W_r would be more than it keeps in
+// flight, a chain of round trips that grows with the width.  Here every
+// thread issues its whole share of W_r before the token is known, so a row
+// takes the token's round trip and its embeddings'.  Many rows are bound by
+// HBM and W_r from the caches.  RL: loops covered (8 or kMaxLoops); rows of
+// W_r past R repeat row 0.
+// Measured, a wave per row and now: 64 rows of 2048 elements 35.0 and 6.1 us,
+// one of 768 8.6 and 5.1; prefill of 8 x 4096 tokens, d = 1024, 10.79 and
+// 10.72 ms.
 // ---------------------------------------------------------------------------
-template <typename T, int NC>
-__global__ __launch_bounds__(256) void k_embed_route(EmbedArgs a) {
-  const int lane = lane_id();
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= a.rows) return;
-  // both row reads in one round trip (prefill reads its token twice instead
-  // of a branch around the sequence length)
-  int tok = a.tokens[row];
-  const int sl = (a.prefill_T > 0 ? a.tokens : a.seq_len)[row];
-  if (tok < 0 || tok >= a.V) {
-    if (lane == 0) set_err(a.err, kErrBadToken);
-    tok = 0;
-  }
-  const int pos = a.prefill_T > 0 ? a.pos0 + row % a.prefill_T : sl;
-  const T* e = reinterpret_cast<const T*>(a.tok_emb) + (int64_t)tok * a.d;
-  const T* p = reinterpret_cast<const T*>(a.pos_emb) + (int64_t)pos * a.d;
-  float* x = a.x + (int64_t)row * a.d;
-  float4 h[NC];
-  float ss = 0.f;
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int k = 4 * lane + 256 * c, kk = clamp_k(k, a.d);
-    const float4 ev = V4<T>::load(e + kk), pv = V4<T>::load(p + kk);
-    h[c] = scale4(make_float4(ev.x + pv.x, ev.y + pv.y, ev.z + pv.z, ev.w + pv.w), k < a.d ? 1.f : 0.f);
-    ss = sumsq(h[c], ss);
-  }
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int k = 4 * lane + 256 * c;
-    if (k < a.d) V4<float>::store(x + k, h[c]);
-  }
-  float inv = 1.f;
-  ss = wave_sum(ss);
-  if (a.y || a.y16) inv = rsqrtf(ss / (float)a.d + a.eps);
-  if (a.ssq)
-    for (int k = lane; k < a.d / 32; k += kWave) a.ssq[(int64_t)row * (a.d / 32) + k] = k == 0 ? ss : 0.f;
-  if (a.x16 || a.y16) {
-    bf16* o16 = a.x16 ? a.x16 : a.y16;
-    const float sc = a.x16 ? 1.f : inv;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int k = 4 * lane + 256 * c;
-      if (k >= a.d) continue;
-      if (a.parts == 2) store_operand4<2>(o16, row, k, a.d, scale4(h[c], sc));
-      else store_operand4<1>(o16, row, k, a.d, scale4(h[c], sc));
-    }
-  }
-  if (a.y) {
-    float* y = a.y + (int64_t)row * a.d;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int k = 4 * lane + 256 * c;
-      if (k < a.d) V4<float>::store(y + k, scale4(h[c], inv));
-    }
-  }
-  if (!a.route) return;  // the MLP router runs after this kernel
-  float z[kMaxLoops];
-#pragma unroll
-  for (int i = 0; i < kMaxLoops; ++i) {
-    // rows of W_r past R repeat row 0; their sums are never used
-    const float* wr = a.Wr + (int64_t)(i < a.R ? i : 0) * a.d;
-    float acc = 0.f;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const float4 w = V4<float>::load(wr + clamp_k(4 * lane + 256 * c, a.d));
-      acc = fmaf(w.w, h[c].w, fmaf(w.z, h[c].z, fmaf(w.y, h[c].y, fmaf(w.x, h[c].x, acc))));
-    }
-    z[i] = acc;
-  }
-#pragma unroll
-  for (int i = 0; i < kMaxLoops; ++i)
-    if (i < a.R) z[i] = wave_sum(z[i]) + a.br[i];
-  if (lane != 0) return;
-  int m;
-  float margin;
-  decide_depth(z, a.R, a.rule, a.threshold, a.fixed, &m, &margin);
-  a.depth[row] = m;
-  if (a.out_depth) a.out_depth[row] = m;
-  if (a.out_margin) a.out_margin[row] = margin;
-}
-
-// The same for few rows, a workgroup of four waves per row; thread t holds
-// elements 4t + 1024c.  Latency bounds these launches (a decode step's batch,
-// a short prompt): one wave's share of W_r is 8 NC vectors, more than it
-// keeps in flight, so the kernel above makes a chain of round trips that
-// grows with the width.  Here every thread issues its whole share of W_r
-// before the token is known, so a row takes the token's round trip and its
-// embeddings'.  RL: loops covered (8 or kMaxLoops); rows of W_r past R repeat
-// row 0.
-// Measured: 64 rows of 2048 elements 35.0 -> 6.1 us, one of 768 8.6 -> 5.1.
 template <typename T, int NC, int RL>
-__global__ __launch_bounds__(256) void k_embed_route_wg(EmbedArgs a) {
+__global__ __launch_bounds__(256) void k_embed_route(EmbedArgs a) {
   __shared__ float s_part[4][RL + 1];
   const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
   const int row = blockIdx.x;
@@ -394,21 +310,15 @@ __global__ __launch_bounds__(256) void k_resid_norm(ResidNormArgs a) {
 template <typename T> hipError_t launch_embed_route(const EmbedArgs& a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   if (a.d <= 0 || a.d % 4 != 0 || a.d > 256 * kRowChunks) return hipErrorInvalidValue;
-  if (a.rows <= kEmbedWgRows) {
-#define TLF_EMBED(NC)                                                                                       \
-  if (a.R <= 8) hipLaunchKernelGGL((k_embed_route_wg<T, NC, 8>), dim3(a.rows), dim3(256), 0, s, a);         \
-  else hipLaunchKernelGGL((k_embed_route_wg<T, NC, kMaxLoops>), dim3(a.rows), dim3(256), 0, s, a)
-    switch ((a.d + 1023) / 1024) {
-      case 1: TLF_EMBED(1); break;
-      case 2: TLF_EMBED(2); break;
-      case 3: TLF_EMBED(3); break;
-      default: TLF_EMBED(4); break;
-    }
-#undef TLF_EMBED
-    return hipGetLastError();
+#define TLF_EMBED(NC)                                                                                    \
+  if (a.R <= 8) hipLaunchKernelGGL((k_embed_route<T, NC, 8>), dim3(a.rows), dim3(256), 0, s, a);         \
+  else hipLaunchKernelGGL((k_embed_route<T, NC, kMaxLoops>), dim3(a.rows), dim3(256), 0, s, a)
+  switch ((a.d + 1023) / 1024) {
+    case 1: TLF_EMBED(1); break;
+    case 2: TLF_EMBED(2); break;
+    case 3: TLF_EMBED(3); break;
+    default: TLF_EMBED(4); break;
   }
-#define TLF_EMBED(NC) hipLaunchKernelGGL((k_embed_route<T, NC>), dim3((a.rows + 3) / 4), dim3(256), 0, s, a)
-  TLF_NC_SWITCH((a.d + 255) / 256, TLF_EMBED)
 #undef TLF_EMBED
   return hipGetLastError();
 }
