@@ -50,11 +50,14 @@ __device__ __forceinline__ unsigned lds_addr(const void* p) {
 // 16 bytes per lane from global memory into 64 consecutive 16-byte LDS chunks
 // from byte `lds` (wave-uniform, in M0).  Assembly, so that the compiler does
 // not wait for every such load before the next LDS read; counts toward vmcnt.
+// A scalar write of M0 needs one wait state before a load into LDS; the
+// compiler, which writes M0 right before the text, inserts it for its own
+// instructions only, so the s_nop is part of the text.
 __device__ __forceinline__ void load_lds16(const void* g, unsigned lds) {
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
 }
 __device__ __forceinline__ void load_lds4(const void* g, unsigned lds) {  // 4 bytes per lane
-  asm volatile("global_load_lds_dword %0, off" ::"v"(g), "{m0}"(lds) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(g), "{m0}"(lds) : "memory");
 }
 // At most N of this wave's vector-memory operations outstanding and its LDS
 // reads done, then the barrier.
