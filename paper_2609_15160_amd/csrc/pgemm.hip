@@ -23,6 +23,8 @@
 // The host does not know a loop's active rows, so the workgroups read the
 // count and take the tile shape from it (pick_shape), and a persistent grid
 // walks the tiles.
+#include <initializer_list>
+
 #include "kernels.h"
 
 namespace tlf {
@@ -106,7 +108,7 @@ __device__ __forceinline__ void pgemm_tile(const GemmArgs& g, int r0, int n0, in
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wk = wave / (SH::WM * WN), wmn = wave % (SH::WM * WN), wm = wmn / WN, wn = wmn % WN;
   const int wbase = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
-  const int S = g.K / 32, KT = S / KSUB;  // the launcher checks K % (32 KSUB) == 0
+  const int S = g.K / 32, KT = S / KSUB;  // whole stages: kStageK
 
   auto key = [](int row) { return P == 2 ? (row >> 1) & 7 : (row >> 2) & 3; };
 
@@ -457,6 +459,17 @@ using PMid = PShape<64, 128, 2, 2, 1, 1, 4>;
 using PSmall = PShape<32, 64, 1, 2, 2, 2, 3>;
 using PTiny = PShape<32, 32, 1, 1, 4, 4, 3>;
 
+// K must be whole stages of the shape with the most K steps per stage: the
+// shape is chosen on the device, and a tile runs K / (32 KSUB) whole stages.
+constexpr int max_ksub(std::initializer_list<int> l) {
+  int m = 0;
+  for (int k : l) m = k > m ? k : m;
+  return m;
+}
+constexpr int kStageK = 32 * max_ksub({PLarge<1>::KSUB, PLarge<2>::KSUB, PWide<1>::KSUB, PWide<2>::KSUB, PMid::KSUB,
+                                       PSmall::KSUB, PTiny::KSUB});
+static_assert(kStageK % (32 * PSmall::KSUB) == 0 && kStageK % (32 * PTiny::KSUB) == 0, "whole stages of every shape");
+
 // Workgroup L runs on XCD L % 8, and each XCD has its own L2.  Up to 3072
 // columns the tiles are dealt to the XCDs as rectangles: RX groups of row
 // tiles times CX = 8 / RX groups of column tiles, so that an XCD reads 1 / RX
@@ -558,7 +571,7 @@ int64_t tile_time(int64_t tiles, int cus, int steps, int t1, int t2, int base) {
 }  // namespace
 
 hipError_t launch_pgemm(const GemmArgs& a, AKind ak, EKind ek, bool norm, int parts, int cus, hipStream_t s) {
-  if (!a.A16 || a.K <= 0 || a.K % 64 != 0 || (a.N % 4 != 0 && ek != E_LOGITS) || cus <= 0) return hipErrorInvalidValue;
+  if (!a.A16 || a.K <= 0 || a.K % kStageK != 0 || (a.N % 4 != 0 && ek != E_LOGITS) || cus <= 0) return hipErrorInvalidValue;
   if (a.rm.rows <= 0 || a.N <= 0) return hipSuccess;
   if (norm && (!a.ssq || a.K > kNormMaxWidth || a.K % 128 != 0)) return hipErrorInvalidValue;
   if (ek == E_RESID && a.out16 && (!a.ssq || a.mod_a || a.N % 32 != 0)) return hipErrorInvalidValue;

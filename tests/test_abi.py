@@ -9,7 +9,7 @@ import tempfile
 import pytest
 
 import synth
-from paper_2609_15160_amd import tlf
+from paper_2609_15160_amd import build, tlf
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -269,3 +269,33 @@ def test_gather_scatter_argument_errors_need_no_device():
     assert lib.tlf_probe_read(dummy, 0, dummy, None) == bad
     assert lib.tlf_probe_read(ctypes.c_void_p(24), g, dummy, None) == bad
     assert lib.tlf_probe_read(dummy, g, None, None) == bad
+
+
+def test_prefill_projection_takes_whole_stages_of_every_tile_shape(lib):
+    """A tile runs K / (K per stage) whole stages, up to 128 elements each, and
+    the shape is chosen on the device: a K that leaves a tail in any of them is
+    refused before anything is launched."""
+    src = r"""
+#include <stdio.h>
+#include "kernels.h"
+int main() {
+  static bf16 dummy[8];
+  tlf::GemmArgs g;
+  g.A16 = dummy; g.W = g.Wf = dummy; g.out = reinterpret_cast<float*>(dummy);
+  g.N = 128; g.ldo = 128; g.rm.rows = 0;  // no rows: an accepted call launches nothing
+  for (int K : {32, 64, 128, 192, 256, 320, 384}) {
+    g.K = K;
+    printf("%d ", (int)tlf::launch_pgemm(g, tlf::A_CMP, tlf::E_RESID, false, 2, 256, nullptr));
+  }
+  return 0;
+}
+"""
+    csrc = os.path.join(ROOT, "paper_2609_15160_amd", "csrc")
+    with tempfile.TemporaryDirectory() as d:
+        cpp, obj, exe = (os.path.join(d, "t" + x) for x in (".hip", ".o", ""))
+        open(cpp, "w").write(src)
+        subprocess.check_call([build.hipcc(), "--offload-arch=gfx950", "-std=c++17", "-I", csrc, "-I",
+                               os.path.join(ROOT, "include"), "-c", cpp, "-o", obj])
+        subprocess.check_call([build.hipcc(), obj, tlf.LIB_PATH, "-Wl,-rpath," + os.path.dirname(tlf.LIB_PATH), "-o", exe])
+        got = [int(v) for v in subprocess.check_output([exe]).decode().split()]
+    assert [v == 0 for v in got] == [False, False, True, False, True, False, True], got
