@@ -268,8 +268,8 @@ struct PrefillPlanArgs {
   int32_t* tok_idx = nullptr;      // [R][G*T]: the loop's gathered rows, compact
   int64_t* kv_slot = nullptr;      // [R][G*T]: cache slot offset of each gathered entry (KvDst)
   int32_t* nact = nullptr;         // [R]: gathered rows of each loop
-  int32_t* seq_cnt = nullptr;      // [G][R]: gathered tokens of each sequence (scratch)
-  int32_t* row_off = nullptr;      // [G][R]: where the sequence's rows start
+  int32_t* seq_cnt = nullptr;      // [G][R]: gathered tokens of each sequence, 0 where its pages did not fit (scratch)
+  int32_t* row_off = nullptr;      // [G][R]: where the sequence's rows start (between the launches its first new page)
 };
 hipError_t launch_plan_prefill(const PrefillPlanArgs& a, hipStream_t s);
 

@@ -245,11 +245,16 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_decode(DecodePlanArgs a) 
 
 // ---------------------------------------------------------------------------
 // Prefill planner, first launch: workgroup g counts sequence b0 + g's tokens
-// per loop (those of depth >= i + 1) into seq_cnt[g][i].
+// per loop (those of depth >= i + 1) into seq_cnt[g][i] and takes the new pages
+// of its caches, the first of each into row_off[g][i].  A loop whose pages do
+// not fit the pool has no rows: its tokens keep the state of the loops that fit.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_plan_count(PrefillPlanArgs a) {
   const int tid = threadIdx.x, g = blockIdx.x, T = a.T, R = a.c.R;
-  __shared__ int hist[kMaxLoops];
+  __shared__ int hist[kMaxLoops], s_np[kMaxLoops];
+  __shared__ int s_base;
+  const int bi = (a.b0 + g) * R + tid;
+  const int old = a.append && tid < R ? a.c.cache_len[bi] : 0;
   if (tid < kMaxLoops) hist[tid] = 0;
   __syncthreads();
   const int32_t* depth = a.depth + (int64_t)g * T;
@@ -267,12 +272,30 @@ __global__ __launch_bounds__(256) void k_plan_count(PrefillPlanArgs a) {
     }
   }
   __syncthreads();
+  int n = 0, np = 0;
   if (tid < R) {
-    int n = 0;
     for (int i = tid; i < R; ++i) n += hist[i];
-    a.seq_cnt[g * R + tid] = n;
+    np = (old + n + kPage - 1) / kPage - (old + kPage - 1) / kPage;  // pages to take
+    s_np[tid] = np;
     atomicAdd(&a.c.depth_hist[tid], (unsigned long long)hist[tid]);
-    if (tid == 0) a.c.seq_len[a.b0 + g] = a.pos0 + T;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int all = 0;
+    for (int i = 0; i < R; ++i) all += s_np[i];
+    s_base = all > 0 ? atomicAdd(a.c.page_next, all) : 0;
+    a.c.seq_len[a.b0 + g] = a.pos0 + T;
+  }
+  __syncthreads();
+  if (tid < R) {
+    int base = s_base;
+    for (int i = 0; i < tid; ++i) base += s_np[i];
+    if (np > 0 && (int64_t)base + np > a.c.max_pages) {
+      set_err(a.c.err, kErrOutOfPages);
+      n = 0;
+    }
+    a.seq_cnt[g * R + tid] = n;
+    a.row_off[g * R + tid] = base;
   }
 }
 
@@ -282,9 +305,10 @@ __global__ __launch_bounds__(256) void k_plan_count(PrefillPlanArgs a) {
 // compact rows that follow the earlier sequences', and places those n entries
 // in slots [n_old, n_old + n) of cache (b, i): n_old = 0 for a new batch, the
 // current length when the call continues the caches (a later prompt chunk).
-// The partly filled last page is used first, then ceil-rounded new pages are
-// taken from the pool; every new slot records its original position
-// (Section 3.3 address translation).  chunk_len[b][i] = n.
+// The partly filled last page is used first, then the new pages that the first
+// launch took; every new slot records its original position (Section 3.3
+// address translation).  chunk_len[b][i] = n, and row_off[g][i] becomes the
+// first of the n rows.
 // ---------------------------------------------------------------------------
 constexpr int kPrePlanThreads = 256, kPrePlanTokens = 4;
 
@@ -295,33 +319,22 @@ __global__ __launch_bounds__(kPrePlanThreads) void k_plan_prefill(PrefillPlanArg
   const int b = a.b0 + g, bi = b * R + i;
   const int64_t GT = (int64_t)a.G * T;
   __shared__ int scan_tmp[kPrePlanThreads / kWave + 1];
-  __shared__ int s_base;
-  const int n = a.seq_cnt[g * R + i];
+  const int n = a.seq_cnt[g * R + i], base = a.row_off[g * R + i];
   const int old = a.append ? c.cache_len[bi] : 0;
   const int p_old = (old + kPage - 1) / kPage;           // pages already holding entries
-  const int np = (old + n + kPage - 1) / kPage - p_old;  // pages to take
-  if (tid == 0) {
-    int base = np > 0 ? atomicAdd(c.page_next, np) : 0;
-    if ((int64_t)base + np > c.max_pages) {
-      set_err(c.err, kErrOutOfPages);
-      base = -1;
-    }
-    s_base = base;
-  }
+  const int np = (old + n + kPage - 1) / kPage - p_old;  // new pages, base .. base + np - 1
   // rows of the earlier sequences
   int before = 0;
   for (int gg = tid; gg < g; gg += kPrePlanThreads) before += a.seq_cnt[gg * R + i];
   int off;
-  block_exclusive_scan(before, scan_tmp, &off);  // (a barrier: s_base is written)
-  const int base = s_base;
+  block_exclusive_scan(before, scan_tmp, &off);
   int32_t* pt = c.page_table + (int64_t)bi * c.pages_per_seq;
-  // the partly filled last page (base >= 0 or not, its slots are the cache's own)
   const int last_page = old % kPage != 0 ? pt[p_old - 1] : -1;
   int32_t* idx = a.tok_idx + (int64_t)i * GT + off;
   int64_t* ks = a.kv_slot + (int64_t)i * GT + off;
   const int32_t* depth = a.depth + (int64_t)g * T;
   int e0 = 0;
-  for (int t0 = 0; t0 < T; t0 += kPrePlanThreads * kPrePlanTokens) {
+  for (int t0 = 0; n > 0 && t0 < T; t0 += kPrePlanThreads * kPrePlanTokens) {
     const int tb = t0 + tid * kPrePlanTokens;
     int f[kPrePlanTokens], cnt = 0, tot;
 #pragma unroll
@@ -335,24 +348,21 @@ __global__ __launch_bounds__(kPrePlanThreads) void k_plan_prefill(PrefillPlanArg
     for (int u = 0; u < kPrePlanTokens; ++u) {
       if (!f[u]) continue;
       const int s = old + e, pi = s / kPage;
-      const int page = base < 0 ? -1 : pi < p_old ? last_page : base + (pi - p_old);
+      const int page = pi < p_old ? last_page : base + (pi - p_old);
       idx[e] = g * T + tb + u;
-      ks[e] = page < 0 ? -1 : (int64_t)page * c.page_elems + s % kPage;
-      if (page >= 0) c.pos[(int64_t)page * kPage + s % kPage] = a.pos0 + tb + u;
+      ks[e] = (int64_t)page * c.page_elems + s % kPage;
+      c.pos[(int64_t)page * kPage + s % kPage] = a.pos0 + tb + u;
       ++e;
     }
     e0 += tot;
   }
-  if (base >= 0) {
-    for (int p = tid; p < np; p += kPrePlanThreads) pt[p_old + p] = base + p;
-    // slots of the last new page past the last entry are marked empty
-    const int s = old + n + tid;
-    if (np > 0 && tid < kPage && s < (p_old + np) * kPage) c.pos[(int64_t)(base + np - 1) * kPage + s % kPage] = -1;
-  }
+  for (int p = tid; p < np; p += kPrePlanThreads) pt[p_old + p] = base + p;
+  // slots of the last new page past the last entry are marked empty
+  const int s = old + n + tid;
+  if (np > 0 && tid < kPage && s < (p_old + np) * kPage) c.pos[(int64_t)(base + np - 1) * kPage + s % kPage] = -1;
   if (tid == 0) {
-    const int nn = base < 0 ? 0 : n;
-    c.cache_len[bi] = old + nn;
-    c.chunk_len[bi] = nn;
+    c.cache_len[bi] = old + n;
+    c.chunk_len[bi] = n;
     a.row_off[g * R + i] = off;
     if (g == a.G - 1) a.nact[i] = off + n;
   }

@@ -896,6 +896,35 @@ def test_out_of_pages_on_append_detected():
         s.close()
 
 
+@pytest.mark.parametrize("kind", ["f32-few-rows", "f32", "bf16-few-rows", "bf16", "bf16-one-part"])
+def test_out_of_pages_in_a_later_loop_keeps_the_loops_that_fit(kind):
+    """A prompt that fits the pool in loop 1 but not in loop 2: loop 2 has no
+    rows, the logits are those of depth 1 to the bit."""
+    import torch
+    from paper_2609_15160_amd import tlf
+    if kind.startswith("f32"):
+        m = _f32_small(batch=1, prompt_len=33 if "few" in kind else 2100, max_loops=2)
+    else:
+        m = synth.CONFIGS["bf16_d768_b32x512"].replace(batch=1, prompt_len={"bf16-few-rows": 100, "bf16": 500}.get(kind, 2100),
+                                                       max_loops=2, n_layers=1)
+    T, pages = m.prompt_len, -(-m.prompt_len // 16)
+    w = synth.make_weights(m)
+    prompts = torch.from_numpy(synth.make_prompts(m).astype(np.int32)).cuda()
+    logits = []
+    for depth, max_pages in ((1, pages), (2, 2 * pages - 1)):
+        s = _session(m, w, max_batch=1, max_pos=T + 1, max_pages=max_pages, route_rule="fixed", fixed_depth=depth,
+                     max_prefill_tokens=T, prefill_act_bf16=kind == "bf16-one-part")
+        try:
+            lg, _ = s.prefill(prompts)
+            logits.append(lg.cpu().numpy())
+            st = s.stats()
+            assert st["status"] == (tlf.OK if depth == 1 else tlf.E_OUT_OF_PAGES)
+            assert list(st["slots_per_loop"][:2]) == [T, 0]
+        finally:
+            s.close()
+    assert np.array_equal(logits[0], logits[1])
+
+
 def test_bad_token_reported():
     import torch
     from paper_2609_15160_amd import tlf
