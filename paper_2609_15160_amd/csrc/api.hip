@@ -181,7 +181,7 @@ struct tlf_ctx {
   bool prefilled = false, poisoned = false;
   int sticky = TLF_OK;
   int cus = 0;  // compute units of the device
-  PgemmShapes shapes[2][5];  // prefill tile shapes with one and two parts: QKV, O, gate/up, down, LM head
+  PgemmShapes shapes[2][5];  // bf16 models: prefill tile shapes with one and two parts: QKV, O, gate/up, down, LM head
   int attn_blocks[2] = {1, 1};  // resident decode-attention workgroups per CU (4 and 8 waves)
   // measurement: event pairs around decode-attention launches, resolved by tlf_cache_stats
   bool profiling = false;     // decode steps launched eagerly, block region timed
@@ -688,7 +688,7 @@ int tlf_init(const tlf_config* cfg, const tlf_weights* w, void* d_workspace, siz
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) { delete ctx; return TLF_E_HIP; }
   ctx->cus = std::max(1, cus);
-  {
+  if (cfg->dtype == TLF_DTYPE_BF16) {
     const int d = cfg->d_model, F = cfg->d_ff;
     const int N[5] = {3 * d, d, 2 * F, d, cfg->vocab}, K[5] = {d, d, d, F, d};
     for (int p = 1; p <= 2; ++p)

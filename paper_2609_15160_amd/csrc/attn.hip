@@ -415,7 +415,7 @@ __global__ __launch_bounds__(WV * 64, 2) void k_attn_prefill(AttnPrefillArgs a) 
 
   // q (float32, scaled by log2(e) / sqrt(D) so scores come out in log2
   // units) as the B operand of S^T = K q^T; against bf16 keys it is split
-  // into hi and lo parts, one product each
+  // into hi and lo parts, one product each, or is the one part given
   Frag qf[QN][NQ][KSTEPS];
 #pragma unroll
   for (int qn = 0; qn < QN; ++qn) {
@@ -433,14 +433,8 @@ __global__ __launch_bounds__(WV * 64, 2) void k_attn_prefill(AttnPrefillArgs a) 
         qf[qn][0][ks] = __builtin_bit_cast(Frag, make_uint4(h0.x, h0.y, h1.x, h1.y));
         qf[qn][1][ks] = __builtin_bit_cast(Frag, make_uint4(l0.x, l0.y, l1.x, l1.y));
       } else if constexpr (EPL == 8) {
-        if (a.q16) {  // written scaled and rounded by the QKV projection
-          qf[qn][0][ks] = *reinterpret_cast<const Frag*>(a.q16 + qo + ks * KS);
-        } else {
-          const float4 v0 = scale4(*reinterpret_cast<const float4*>(qp + ks * KS), a.scale_log2);
-          const float4 v1 = scale4(*reinterpret_cast<const float4*>(qp + ks * KS + 4), a.scale_log2);
-          qf[qn][0][ks] = __builtin_bit_cast(Frag, make_uint4(pack_bf16x2(v0.x, v0.y), pack_bf16x2(v0.z, v0.w),
-                                                              pack_bf16x2(v1.x, v1.y), pack_bf16x2(v1.z, v1.w)));
-        }
+        // written scaled and rounded by the QKV projection
+        qf[qn][0][ks] = *reinterpret_cast<const Frag*>(a.q16 + qo + ks * KS);
       } else {
         qf[qn][0][ks] = qp[ks * KS] * a.scale_log2;
       }
@@ -753,7 +747,7 @@ hipError_t attn_decode_blocks_per_cu(int D, int waves, int* blocks) {
 // 8 and 4 waves): 1 x 1000 tokens 22.1 and 20.4, 3 x 777 20.5 and
 // 20.1, the later loops of both 5 to 12% less with 4.
 template <typename T, int D, bool SPLITQ>
-hipError_t launch_prefill_d(const AttnPrefillArgs& a, hipStream_t s) {
+hipError_t launch_prefill_waves(const AttnPrefillArgs& a, hipStream_t s) {
   auto blocks = [&](int waves) { return (int64_t)a.G * ((a.T + waves * kPreQW - 1) / (waves * kPreQW)) * a.c.H; };
   if (blocks(8) < 2 * (int64_t)a.cus)
     hipLaunchKernelGGL((k_attn_prefill<T, D, SPLITQ, 4>), dim3((unsigned)blocks(4)), dim3(256), 0, s, a);
@@ -762,18 +756,25 @@ hipError_t launch_prefill_d(const AttnPrefillArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// One part of q exists for bf16 keys only.
+template <typename T, int D>
+hipError_t launch_prefill_d(const AttnPrefillArgs& a, hipStream_t s) {
+  if constexpr (sizeof(T) == 2) {
+    if (a.q16) return launch_prefill_waves<T, D, false>(a, s);
+  }
+  return launch_prefill_waves<T, D, true>(a, s);
+}
+
 template <typename T>
 hipError_t launch_attn_prefill(const AttnPrefillArgs& a, hipStream_t s) {
   if (a.G <= 0) return hipSuccess;
   // a 16-wide head needs the 4-deep f32 MFMA; bf16 models reject head_dim 16
   switch (a.c.D) {
     case 16:
-      if constexpr (sizeof(T) == 4) return launch_prefill_d<T, 16, true>(a, s);
+      if constexpr (sizeof(T) == 4) return launch_prefill_d<T, 16>(a, s);
       return hipErrorInvalidValue;
-    case 64:
-      return sizeof(T) == 2 && a.q16 ? launch_prefill_d<T, 64, false>(a, s) : launch_prefill_d<T, 64, true>(a, s);
-    case 128:
-      return sizeof(T) == 2 && a.q16 ? launch_prefill_d<T, 128, false>(a, s) : launch_prefill_d<T, 128, true>(a, s);
+    case 64: return launch_prefill_d<T, 64>(a, s);
+    case 128: return launch_prefill_d<T, 128>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -264,16 +264,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int r0, const
 
   const int col16 = lane & 15;
   if constexpr (EK == E_QKV) {
-    // q to its buffer; k and v into the cache pages.  A 16-column tile lies
-    // in one of q, k and v (d is a multiple of 16).  q and (bf16) k tiles go
-    // through an in-group 4 x 4 transpose, after which lane t holds four
-    // consecutive columns of row 4 quad + t: one 16-byte q store, or one
-    // 8-byte k store (four dimensions of one slot are adjacent in the
-    // fragment order).  A v tile keeps the lane's column: when its four rows
-    // are consecutive slots of one page from a multiple of 4 (a fresh
-    // prefill), their values of that dimension are one aligned run in the V
-    // block and go out as one store; otherwise element by element.  The
-    // tile's part, head and first dimension are resolved once per tile.
+    // q to its buffer; k and v into the cache pages (float32 models).  A
+    // 16-column tile lies in one of q, k and v (d is a multiple of 16).  A q
+    // tile goes through an in-group 4 x 4 transpose, after which lane t holds
+    // four consecutive columns of row 4 quad + t: one 16-byte store.  k and v
+    // tiles keep the lane's column: when the four rows of a v tile are
+    // consecutive slots of one page from a multiple of 4 (a fresh prefill),
+    // their values of that dimension are one aligned run in the V block and go
+    // out as one store; otherwise element by element.  The tile's part, head
+    // and first dimension are resolved once per tile.
+    static_assert(sizeof(T) == 4, "bf16 models: pgemm.hip");
     T* pool = reinterpret_cast<T*>(g.kv.c.pool);
     const int t = col16 & 3;
 #pragma unroll
@@ -288,22 +288,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int r0, const
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         const int rl0 = wm * MT * 16 + i * 16 + quad * 4;
-        if (part == 0 || (sizeof(T) == 2 && part == 1)) {
+        if (part == 0) {
           float v0 = acc[i][j][0], v1 = acc[i][j][1], v2 = acc[i][j][2], v3 = acc[i][j][3];
           transpose4(v0, v1, v2, v3, t);
           const int rl = rl0 + t, cw = col16 & ~3;  // the lane's first column in the tile
-          if (part == 0) {
-            if (row_src_s[rl] >= 0) {
-              *reinterpret_cast<float4*>(reinterpret_cast<float*>(g.out) + (int64_t)(r0 + rl) * g.ldo + nt + cw) =
-                  make_float4(v0, v1, v2, v3);
-            }
-          } else {
-            const int64_t base = kv_base[rl];
-            if (base >= 0) {
-              const int slot = (int)(base & (kPage - 1));
-              T* dst = pool + (base - slot) + kvb + k_frag_off<T>(slot, e0 + cw);
-              *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
-            }
+          if (row_src_s[rl] >= 0) {
+            *reinterpret_cast<float4*>(reinterpret_cast<float*>(g.out) + (int64_t)(r0 + rl) * g.ldo + nt + cw) =
+                make_float4(v0, v1, v2, v3);
           }
           continue;
         }
@@ -314,12 +305,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int r0, const
         if (run4) {
           const int slot = (int)(b0 & (kPage - 1));
           T* dst = pool + (b0 - slot) + kvb + v_frag_off(slot, e, g.kv.c.D);
-          if constexpr (sizeof(T) == 2) {
-            *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(acc[i][j][0], acc[i][j][1]),
-                                                        pack_bf16x2(acc[i][j][2], acc[i][j][3]));
-          } else {
-            *reinterpret_cast<float4*>(dst) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-          }
+          *reinterpret_cast<float4*>(dst) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
           continue;
         }
 #pragma unroll
