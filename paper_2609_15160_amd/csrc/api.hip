@@ -364,6 +364,10 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     // saves: then a norm kernel writes the normalised operand after each of them
     const bool fused = parted && !c.adaln && rows <= kPrefillFusedNormRows && ctx->L.size[B_SSQ] > 0;
     float* ssq = fused ? ctx->buf<float>(B_SSQ) : nullptr;
+    // whether the LM head reads the rows that the last residual projection
+    // leaves for it: few rows (and one part, AdaLN) are normalised from x
+    const int head_rows = (flags & TLF_PREFILL_ALL_LOGITS) != 0 ? rows : Gc;
+    const bool head_reads = !few && head_rows >= kHeadGemmRows && !(parted && (parts == 1 || c.adaln));
     bf16* y16 = parted ? ctx->buf<bf16>(B_Y_PRE) : nullptr;
     bf16* o16 = parted ? ctx->buf<bf16>(B_O_PRE) : nullptr;
     bf16* act16 = parted ? ctx->buf<bf16>(B_ACT_PRE) : nullptr;
@@ -393,9 +397,10 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     pa.row_off = ctx->buf<int32_t>(B_PRE_OFF);
     TLF_HIP(launch_plan_prefill(pa, s));
 
-    // float32 or AdaLN models: RMSNorm(x) after a residual projection, for the projection at (loop ni,
-    // layer nj) that reads it next: with operand rows its AdaLN scale (table
-    // part 2 QKV, 3 gate/up) is applied here
+    // neither few rows nor the norm fused: RMSNorm(x) after a residual
+    // projection, for the projection at (loop ni, layer nj) that reads it next:
+    // with operand rows its AdaLN scale (table part 2 QKV, 3 gate/up) is
+    // applied here
     ResidNormArgs rn;
     rn.x = x; rn.y = parted ? nullptr : y; rn.y16 = y16; rn.parts = parts; rn.d = d; rn.eps = c.rms_eps;
     auto norm = [&](const RowMap& rm, int ni, int nj, int part) {
@@ -468,24 +473,25 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
         GemmArgs dn;
         dn.A = ctx->buf<float>(B_ACT_PRE); dn.lda = F; dn.W = lw.w_down; dn.Wf = ctx->wfrag(j, 3); dn.N = d; dn.K = F; dn.w_rows = d;
         dn.rm = rm; dn.out = x; dn.ldo = d; dn.scatter = 1; dn.spec = i == 0; dn.A16 = act16;
-        dn.shapes = shapes[3]; dn.out16 = fused ? y16 : nullptr; dn.ssq = ssq;
+        const bool last = j + 1 == c.n_layers, read = i + 1 < R || !last || head_reads;
+        dn.shapes = shapes[3]; dn.out16 = fused && read ? y16 : nullptr; dn.ssq = ssq;
         set_mod(ctx, &dn, i, j, 1, pre_depth, 1);
         TLF_HIP(project(dn, A_CMP, E_RESID));
-        const bool last = j + 1 == c.n_layers;
-        if (!few && !fused) TLF_HIP(norm(rm, last ? i + 1 : i, last ? 0 : j + 1, 2));
+        if (!few && !fused && read) TLF_HIP(norm(rm, last ? i + 1 : i, last ? 0 : j + 1, 2));
       }
     }
     GemmArgs hd;
     hd.A = x; hd.lda = d; hd.W = head_weights(ctx); hd.N = c.vocab; hd.K = d; hd.w_rows = c.vocab;
     hd.out = logits; hd.ldo = c.vocab; hd.eps = c.rms_eps; hd.spec = 1;
+    hd.rm.rows = head_rows;
     if (flags & TLF_PREFILL_ALL_LOGITS) {
-      hd.rm.rows = rows; hd.rm.src_stride = 1; hd.rm.src_off = 0;
+      hd.rm.src_stride = 1; hd.rm.src_off = 0;
       hd.out_row_off = b0 * T_;
     } else {
-      hd.rm.rows = Gc; hd.rm.src_stride = T_; hd.rm.src_off = T_ - 1;
+      hd.rm.src_stride = T_; hd.rm.src_off = T_ - 1;
       hd.out_row_off = b0;
     }
-    if (few || hd.rm.rows < kHeadGemmRows) {  // the norm fused
+    if (few || head_rows < kHeadGemmRows) {  // the norm fused
       TLF_HIP(launch_dgemm<T>(hd, A_SRC, E_LOGITS, true, ctx->cus, s));
     } else if (parted) {
       const bool hn = fused && parts == 2;
