@@ -625,6 +625,14 @@ def counter_summary(fetch_csv, write_csv, first, count, bench_json, window):
                            f"{wcopy:.1f} KiB WRITE_SIZE"}
 
 
+# kernels of a prefill's projections and LM head: bf16 models, float32 rows, few rows
+PREFILL_GEMMS = ("k_pgemm", "k_gemm", "k_dgemm")
+
+
+def is_prefill_gemm(name):
+    return any(k in name for k in PREFILL_GEMMS)
+
+
 def mfma_summary(counter_csv):
     """MFMA activity of the prefill from a rocprofv3 --pmc run of
     `bench.py --prefill-only` that collected MfmaUtil and MfmaFlopsBF16.
@@ -656,7 +664,7 @@ def mfma_summary(counter_csv):
         a = bounds[p]
         while a > 0 and "k_fill" in rows[a - 1]["name"]:
             a -= 1
-        gemms = [i for i in range(bounds[p], bounds[p + 1]) if "k_gemm" in rows[i]["name"]]
+        gemms = [i for i in range(bounds[p], bounds[p + 1]) if is_prefill_gemm(rows[i]["name"])]
         return rows[a:gemms[-1] + 1]
     out = {}
     for label, first in (("one_part", 1), ("hi_lo_parts", 5)):
@@ -703,15 +711,15 @@ def prefill_trace_summary(trace_csv, loops, layers, first=1, count=3):
     for pf in range(first, first + count):
         a = plans[pf]
         b = plans[pf + 1] if pf + 1 < len(plans) else len(rows)
-        blk = [r for r in rows[a + 1:b] if "k_gemm" in r["Kernel_Name"] or "k_attn_prefill" in r["Kernel_Name"]]
+        blk = [r for r in rows[a + 1:b] if is_prefill_gemm(r["Kernel_Name"]) or "k_attn_prefill" in r["Kernel_Name"]]
         blk = blk[:loops * layers * 5]
         for q, r in enumerate(blk):
             i, rem = divmod(q, layers * 5)
             per[(i, names[rem % 5])].append(dur(r))
         # span: from the first kernel after the previous prefill's last GEMM
         # (its LM head) to this prefill's LM head
-        prev = max(k for k in range(plans[pf - 1], a) if "k_gemm" in rows[k]["Kernel_Name"])
-        end = max(k for k in range(a, b) if "k_gemm" in rows[k]["Kernel_Name"])
+        prev = max(k for k in range(plans[pf - 1], a) if is_prefill_gemm(rows[k]["Kernel_Name"]))
+        end = max(k for k in range(a, b) if is_prefill_gemm(rows[k]["Kernel_Name"]))
         spans.append((int(rows[end]["End_Timestamp"]) - int(rows[prev + 1]["Start_Timestamp"])) / 1e3)
     table = [{"loop": i + 1, **{n: sum(per[(i, n)]) / len(per[(i, n)]) for n in names if per[(i, n)]}}
              for i in range(loops)]
