@@ -484,51 +484,90 @@ def test_bf16_prefill_single_part_activations_d768():
     _check_bf16(m, w, prompts, g, o, sample, "bf16-prefill-one-part-d768")
 
 
-@pytest.mark.parametrize("act16", [False, True], ids=["two-parts", "one-part"])
-@pytest.mark.parametrize("batch,prompt_len", [(1, 65), (2, 33), (3, 43), (5, 26), (2, 256), (9, 151), (40, 200)])
-def test_bf16_prefill_row_tile_edges(batch, prompt_len, act16):
-    """Compact rows of the prefill projections around the tile edges (65, 66,
-    129, 130, 512, 1359 and 8000 rows in the first loop, ragged counts in the
-    later ones, sequences that share a tile; four and, for the last, two key
-    groups in the attention), a vocabulary that fits no tile and a one-tile
-    model width: every position's logits and two decode steps against
-    the oracle, every cache index."""
+@pytest.mark.parametrize("batch,prompt_len", [(1, 65), (2, 33), (3, 43), (5, 26), (2, 256), (9, 151)])
+def test_bf16_prefill_few_rows_of_several_sequences(batch, prompt_len):
+    """Prefill projections on the split-K kernel (65, 66, 129, 130, 512 and
+    1359 rows of a 128-wide model in the first loop, ragged counts in the later
+    ones, sequences that share a tile), a vocabulary that fits no tile: every
+    position's logits and two decode steps against the oracle, every cache index."""
     m = synth.ModelConfig("bf16-d128", "bf16", vocab=509, d_model=128, n_heads=2, head_dim=64, d_ff=384,
                           n_layers=2, max_loops=5, batch=batch, prompt_len=prompt_len, steps=2,
                           router_bias="calibrated")
+    assert batch * prompt_len * m.d_model <= parity.FEW_ROW_ELEMS
     w = synth.make_weights(m)
     prompts = synth.make_prompts(m)
-    sample = list(range(batch))
-    g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, all_logits=True, prefill_act_bf16=act16)
+    g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, all_logits=True)
     o = parity.run_oracle(m, w, prompts, g.step_tokens, all_logits=True)
-    _check_bf16(m, w, prompts, g, o, sample, f"bf16-row-tiles-{batch}x{prompt_len}-{act16}")
+    _check_bf16(m, w, prompts, g, o, list(range(batch)), f"bf16-few-rows-{batch}x{prompt_len}")
 
 
-@pytest.mark.parametrize("prompt_len", [60, 230, 700])
+@pytest.mark.parametrize("act16", [False, True], ids=["two-parts", "one-part"])
+@pytest.mark.parametrize("d,batch,prompt_len",
+                         [(768, 3, 86), (768, 11, 29), (768, 3, 107), (768, 5, 77), (768, 3, 171), (768, 25, 41),
+                          (768, 7, 390), (768, 4, 1024), (768, 3, 1367), (640, 3, 103), (640, 4, 1000), (1024, 3, 65),
+                          (128, 40, 200)])
+def test_bf16_prefill_row_tile_edges(d, batch, prompt_len, act16):
+    """Compact rows of the tiled prefill projections around the edges of their
+    row tiles (258, 319, 321, 385, 513, 1025, 2730, 4096, 4101, 309, 4000, 195
+    and 8000 rows in the first loop, ragged counts in the later ones, sequences
+    that share a tile), with the norm fused (up to 4096 rows) and not, four or
+    eight waves per workgroup in the attention, a vocabulary that fits no tile:
+    every position's logits and two decode steps against the oracle, every cache
+    index."""
+    rows, d_ff = batch * prompt_len, 1664 if d == 640 else 384
+    m = synth.ModelConfig(f"bf16-d{d}", "bf16", vocab=509, d_model=d, n_heads=d // 64, head_dim=64, d_ff=d_ff,
+                          n_layers=1, max_loops=5, batch=batch, prompt_len=prompt_len, steps=2,
+                          router_bias="calibrated")
+    assert rows * d > parity.FEW_ROW_ELEMS
+    w = synth.make_weights(m)
+    prompts = synth.make_prompts(m)
+    g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, all_logits=True, prefill_act_bf16=act16)
+    o = parity.run_oracle(m, w, prompts, g.step_tokens, all_logits=True, threads=4)
+    parts = 1 if act16 else 2
+    tiles = {parity.prefill_tile(N, K, parts, int((g.prefill_depths >= i).sum()), 65536)
+             for i in range(1, m.max_loops + 1) for N, K in ((3 * d, d), (d, d), (2 * d_ff, d), (d, d_ff))
+             if (g.prefill_depths >= i).any()}
+    _report(f"row-tiles-{d}-{batch}x{prompt_len}", rows=rows, fused=rows <= parity.FUSED_NORM_ROWS, tiles=sorted(tiles))
+    _check_bf16(m, w, prompts, g, o, list(range(batch)), f"bf16-row-tiles-{d}-{batch}x{prompt_len}-{act16}")
+
+
+@pytest.mark.parametrize("prompt_len", [700, 2048, 2049])
 def test_bf16_prefill_single_sequence_keeps_two_parts(prompt_len):
     """A single sequence of at most 2048 tokens takes two bf16 parts per
-    activation with prefill_act_bf16 as without: the same bits."""
-    m = synth.CONFIGS["bf16_d768_b32x512"].replace(batch=1, prompt_len=prompt_len, steps=1)
+    activation with prefill_act_bf16 as without, the same bits; one token more
+    takes one part."""
+    m = synth.CONFIGS["bf16_d768_b32x512"].replace(batch=1, prompt_len=prompt_len, steps=1, n_layers=1)
+    assert prompt_len * m.d_model > parity.FEW_ROW_ELEMS
     w = synth.make_weights(m)
     prompts = synth.make_prompts(m)
-    a, b = (parity.run_gpu(m, w, prompts, 1, max_pos=m.max_pos, prefill_act_bf16=x) for x in (False, True))
-    assert np.array_equal(a.prefill_logits, b.prefill_logits)
-    assert np.array_equal(a.step_logits[0], b.step_logits[0])
+    two, one = (parity.run_gpu(m, w, prompts, 1, max_pos=m.max_pos, prefill_act_bf16=x) for x in (False, True))
+    same = prompt_len <= 2048
+    assert np.array_equal(two.prefill_logits, one.prefill_logits) == same
+    assert np.array_equal(two.step_logits[0], one.step_logits[0]) == same
+    if not same:
+        for g in (two, one):
+            o = parity.run_oracle(m, w, prompts, g.step_tokens)
+            _check_bf16(m, w, prompts, g, o, [0], f"bf16-one-sequence-{prompt_len}")
 
 
-def test_bf16_prefill_single_part_ragged_wide_tiles():
-    """One-part bf16 prefill activations on a model whose widths leave ragged
-    256-column tiles (d 640 = 5 x 128 heads, QKV 1920 columns, SwiGLU 1664)
-    with 4 x 1100 rows, enough for the 256 x 256 GEMM tiles; all sequences'
-    last-position logits and four decode steps against the oracle."""
+@pytest.mark.parametrize("act16", [False, True], ids=["two-parts", "one-part"])
+def test_bf16_prefill_ragged_wide_tiles(act16):
+    """128 x 256 tiles on widths that leave a ragged last column tile (d 640 =
+    5 x 128 heads: QKV 1920 columns, and with one part the down projection's
+    640, in the first loop's 4 x 1700 rows): all sequences' last-position logits,
+    every cache index and four decode steps (over the cached keys and values)
+    against the oracle."""
     m = synth.ModelConfig("bf16-d640", "bf16", vocab=5000, d_model=640, n_heads=5, head_dim=128, d_ff=1664,
-                          n_layers=2, max_loops=6, batch=4, prompt_len=1100, steps=4, router_bias="calibrated")
+                          n_layers=2, max_loops=6, batch=4, prompt_len=1700, steps=4, router_bias="calibrated")
+    rows = m.batch * m.prompt_len
+    wide = [parity.prefill_tile(N, K, 1 if act16 else 2, rows, 65536) for N, K in ((1920, 640), (640, 1664))]
+    assert wide == ([(128, 256), (128, 256)] if act16 else [(128, 256), (64, 128)])
     w = synth.make_weights(m)
     prompts = synth.make_prompts(m)
     sample = [0, 1, 2, 3]
-    g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, keep_logits_rows=sample, prefill_act_bf16=True)
+    g = parity.run_gpu(m, w, prompts, m.steps, max_pos=m.max_pos, keep_logits_rows=sample, prefill_act_bf16=act16)
     o = parity.run_oracle(m, w, prompts[sample], [t[sample] for t in g.step_tokens], threads=4)
-    _check_bf16(m, w, prompts, g, o, sample, "bf16-prefill-one-part-d640")
+    _check_bf16(m, w, prompts, g, o, sample, f"bf16-prefill-d640-{act16}")
 
 
 def test_bf16_d2048_heads_of_128_small_batch():
@@ -714,9 +753,9 @@ def test_f32_adaln_chunked_prefill_equals_one_shot():
 
 
 def test_bf16_adaln_prefill_single_part():
-    """AdaLN with one-part bf16 prefill activations: the QKV and gate/up rows
-    carry the (1 + gamma) scale, so they are rounded in LDS from the float
-    rows; O and down read bf16 rows and gate with (1 + alpha)."""
+    """AdaLN with one-part bf16 prefill activations: the norm kernel scales the
+    QKV and gate/up rows by (1 + gamma) and rounds them; O and down gate with
+    (1 + alpha)."""
     base = synth.CONFIGS["bf16_d768_b32x512"].replace(adaln=True)
     m = base.replace(batch=4, prompt_len=200, steps=6)
     w = synth.make_weights(base)
