@@ -123,11 +123,13 @@ typedef struct tlf_config {
                             loop i has cumulative time (i-1)/m and step 1/m, and layer j's
                             modulation (alpha_msa, alpha_mlp, gamma_msa, gamma_mlp) enters as
                             x += (1 + alpha) * F(RMSNorm(x) * (1 + gamma)) */
-  int32_t prefill_act_bf16; /* bf16 models, prefills of more than one sequence or longer than 2048
-                               tokens: 0: the float32 activations enter the block's matrix products
-                               and the attention scores as bf16 hi + lo parts; 1: as one bf16 part
-                               (round to nearest even), half the matrix-core work.  Decode steps and
-                               every LM head keep the two parts.  An exact bf16 implementation with
+  int32_t prefill_act_bf16; /* bf16 models: 0: the float32 activations enter the block's matrix
+                               products and the attention scores of a prefill as bf16 hi + lo parts;
+                               1: as one bf16 part (round to nearest even), half the matrix-core
+                               work.  Two parts whatever this says: decode steps, every LM head, and
+                               a prefill group (the sequences that fit max_prefill_tokens together)
+                               of one sequence of at most 2048 tokens or of at most 256 x 768 row
+                               elements (tokens x d_model).  An exact bf16 implementation with
                                every activation rounded stays within 1.9e-2 of float64 on the
                                logits at d_model 1024 but reaches 4.1e-2 at 2048 */
 } tlf_config;
@@ -317,8 +319,9 @@ const char* tlf_status_str(int status);
  * d a multiple of 4).  Token t takes part in loop i exactly when its depth
  * m_t >= i.  Backward passes reuse the same calls: the gradient of the
  * gather is an in-place tlf_gs_scatter of the compact gradient into the row
- * gradients (tlf_gs_expand where there are none yet), and the gradient of the scatter is the incoming gradient itself
- * for the previous state plus its tlf_gs_gather for the block output.
+ * gradients (tlf_gs_expand where there are none yet), and the gradient of the
+ * scatter is the incoming gradient itself for the previous state plus its
+ * tlf_gs_gather for the block output.
  * Argument errors return TLF_E_INVALID_ARG before anything is enqueued; a
  * failed launch returns TLF_E_HIP.  Indices and slots are trusted: they must
  * be what tlf_gs_plan wrote for the same depths.

@@ -34,7 +34,10 @@ struct Layout {
 };
 
 // Prefill groups of at most this many rows fuse the RMSNorm into the
-// projections that read it.
+// projections that read it.  us per prefill without and with it, d = 768, two
+// parts: 400 rows 846 and 784, 1024 1000 and 944, 4096 1908 and 1837, 8192 2967
+// and 2940, 16384 4935 and 4942, 32768 8976 and 9083; d = 1024, one part: 4096
+// 2053 and 1995, 16384 5079 and 5041.
 constexpr int kPrefillFusedNormRows = 4096;
 
 bool make_layout(const tlf_config& c, Layout* L) {
@@ -298,19 +301,27 @@ int attn_waves(const tlf_ctx* ctx) {
   return units * 4 >= slots ? 4 : 8;
 }
 
-// Decode batches of at least this many rows run the LM head on the 128 x 128 GEMM.
+// At least this many rows run the LM head on a tiled GEMM (decode launch_gemm's
+// 128 x 128 tiles; prefill launch_pgemm, or launch_gemm in float32), fewer on
+// the split-K projection.
 constexpr int kHeadGemmRows = 128;
 
 // bf16 prefill groups of at most this many row elements (rows x d_model) run
 // their projections on the split-K decode GEMM, which reads every row once per
-// column tile: one 768-wide sequence of 140, 230 and 300 tokens took 651, 715
-// and 795 us per prefill on it against 699, 735 and 762 us on launch_pgemm, a
-// 2048-wide one of 200 tokens 1832 against 1581 us.
+// column tile.  us per prefill on it and on launch_pgemm, one sequence (four
+// of a quarter of the rows: the same order):
+//   d = 128   1024 rows 576, 605   1536 662, 667   2048 791, 731
+//   d = 256    512      540, 585    768 617, 625   1024 711, 661
+//   d = 512    256      533, 621    384 607, 658    512 702, 689
+//   d = 768    192      619, 681    256 653, 710    320 779, 742
+//   d = 1024   128      726, 750    192 831, 794    256 942, 818
+//   d = 2048    64      957, 1157    96 1170, 1235  128 1341, 1294
 constexpr int64_t kPrefillFewElems = 256 * 768;
 constexpr int kPrefillFewRowsF32 = 2048;  // float32 models: a single sequence of at most this many tokens
 
 // A single sequence of at most this many tokens keeps two bf16 parts per
-// activation whatever prefill_act_bf16 says.
+// activation whatever prefill_act_bf16 says (and so does every group of few
+// rows, whose projections split float32 rows).
 constexpr int kPrefillTwoPartTokens = 2048;
 
 // AdaLN: point a projection at its rows' modulation at (loop i, layer j):
@@ -353,15 +364,16 @@ int run_prefill(tlf_ctx* ctx, int B, int T_, int pos0, const int32_t* tokens, fl
     // fused (x is read through the gathered positions, no y)
     const bool few = c.dtype == TLF_DTYPE_BF16 ? (int64_t)rows * d <= kPrefillFewElems
                                                : Gc == 1 && T_ <= kPrefillFewRowsF32;
-    // bf16 models: x, o and act are handed on as bf16 operand rows of two
-    // parts, or of one (prefill_act_bf16), and the projections normalise x;
-    // the LM head always takes two parts
+    // bf16 models: the projections' operands are handed on as bf16 rows of two
+    // parts, or of one (prefill_act_bf16); the LM head always takes two
     const bool parted = c.dtype == TLF_DTYPE_BF16 && !few;
     const int parts = c.prefill_act_bf16 && !(Gc == 1 && T_ <= kPrefillTwoPartTokens) ? 1 : 2;
     const PgemmShapes* shapes = ctx->shapes[parts - 1];
-    // with AdaLN the operand is RMSNorm(x) (1 + gamma), and with many rows the
-    // extra operand rows cost the residual projections as much as the kernel
-    // saves: then a norm kernel writes the normalised operand after each of them
+    // fused: the residual projections write x itself as the next operand, and
+    // the projections that read it normalise.  With AdaLN the operand is
+    // RMSNorm(x) (1 + gamma), and with many rows the extra operand rows cost the
+    // residual projections as much as the norm kernel does: then that kernel
+    // writes the normalised operand after each of them
     const bool fused = parted && !c.adaln && rows <= kPrefillFusedNormRows && ctx->L.size[B_SSQ] > 0;
     float* ssq = fused ? ctx->buf<float>(B_SSQ) : nullptr;
     // whether the LM head reads the rows that the last residual projection

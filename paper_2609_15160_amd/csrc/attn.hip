@@ -4,17 +4,18 @@
 // of its sequence whose depth is >= i plus itself; exited tokens have no
 // slot, so the validity mask is implicit.  One workgroup of W waves owns a
 // (row, head) of a persistent grid; its page list is staged in LDS, each wave
-// streams a contiguous share of the entries in 16-byte K/V loads (G lanes per
-// token, 64/G tokens per instruction) with two register batches in flight,
-// every lane keeps its own online-softmax state, lanes merge with DPP moves
-// and shuffles, and the W waves merge through LDS with a log-sum-exp combine.
+// streams a contiguous share of the pages in 16-byte K/V loads straight into
+// MFMA operands (S = K q^T and O = V^T P^T, the query the same in all columns)
+// with two register batches in flight where they fit, and the W waves merge
+// through LDS with a log-sum-exp combine.
 // No state crosses workgroups, so no device-scope fence is needed.
 //
 // Prefill: causal attention among the gathered tokens of each loop (Section
 // 3.3), which in compact order is a plain causal mask on the (b, i) slot
-// sequence.  One workgroup per (sequence, 64-query tile, head), 16 queries
-// per wave, the longest query tiles dispatched first.  Key tiles of four pages are copied into LDS verbatim (the K
-// blocks are already in MFMA-fragment order), the next tile loading into
+// sequence.  One workgroup per (sequence, tile of 128 or 64 queries, head), 16
+// queries per wave, the longest query tiles dispatched first.  Key tiles of
+// four pages are copied into LDS verbatim (the K blocks are already in
+// MFMA-fragment order), the next two tiles (float32: the next one) loading into
 // registers while the current one is in use.  Scores are computed transposed,
 // S^T = K q^T, so that the P^T operand of O^T = V^T P^T is exactly the scores
 // each lane holds (no data movement between the two products); both run on
@@ -101,7 +102,9 @@ __device__ __forceinline__ float merge_scale(float m, float mn) {
 // two at head width 128 in bf16, whose two batches in flight (8 KB of K and 8
 // KB of V per wave and batch) take 234 registers; one batch at three waves
 // (168 registers) was slower: 2685 against 2762 us for a decode step of 64
-// sequences x 4096 tokens, d = 2048.
+// sequences x 4096 tokens, d = 2048.  Four in float32 with 8 waves: 100
+// sequences x 1000 tokens of 4 such heads took 732 us a step against 775 with
+// the compiler's own choice, fewer sequences the same.
 template <typename T, int D, int W> constexpr int decode_waves() {
   if (D != 128) return 1;
   return sizeof(T) == 2 ? 2 : W == 8 ? 4 : 1;
@@ -743,9 +746,10 @@ hipError_t attn_decode_blocks_per_cu(int D, int waves, int* blocks) {
 
 // Workgroups of 8 waves share each staged key tile among 128 queries; with
 // fewer than two of them per compute unit, workgroups of 4 waves spread the
-// same waves over more compute units.  Measured (12 x 64 heads, loop 1, us with
-// 8 and 4 waves): 1 x 1000 tokens 22.1 and 20.4, 3 x 777 20.5 and
-// 20.1, the later loops of both 5 to 12% less with 4.
+// same waves over more compute units.  The host counts the workgroups of a loop
+// that every token runs; the later loops, which have fewer, keep that form.
+// Measured (12 x 64 heads, loop 1, us with 8 and 4 waves): 1 x 1000 tokens 22.1
+// and 20.4, 3 x 777 20.5 and 20.1, the later loops of both 5 to 12% less with 4.
 template <typename T, int D, bool SPLITQ>
 hipError_t launch_prefill_waves(const AttnPrefillArgs& a, hipStream_t s) {
   auto blocks = [&](int waves) { return (int64_t)a.G * ((a.T + waves * kPreQW - 1) / (waves * kPreQW)) * a.c.H; };

@@ -598,7 +598,8 @@ hipError_t launch_w(const GemmArgs& a, int cus, hipStream_t s) {
 }  // namespace
 
 // Tile shapes (rows x columns, waves): thin | narrow | wide, narrow and wide
-// measured on the projections of a 256-row batch.
+// measured on the projections of a 256-row batch of the 768-wide model; other
+// widths take the same shapes, by the rule of one workgroup per compute unit.
 //   QKV:     32 x 32 | 32 x 64 | 32 x 80   (8 waves)
 //   gate/up: 32 x 32 | 32 x 64 | 32 x 128  (8 waves)
 //   O:       32 x 16 | 32 x 32             (8 waves)

@@ -142,7 +142,11 @@ template <int P> __device__ __forceinline__ void store_operand4(bf16* p, int64_t
 // Supported: (A_SRC, E_QKV | E_SWIGLU | E_LOGITS, norm or not), (A_CMP,
 // E_RESID, no norm).  norm: the rows hold the residual x and the product is
 // taken with RMSNorm(x).
-constexpr int kNormMaxWidth = 1024;  // widest rows of launch_pgemm's norm
+// Widest rows of launch_pgemm's norm: each column tile reads its rows' sums of
+// squares.  At d = 2048 it was a gain for few rows only: 1 x 200 tokens 1498 ->
+// 1422 us, 1 x 512 2142 -> 2048, 4 x 1000 7280 -> 7337, 2 x 1500 with one part
+// 4581 -> 4806.
+constexpr int kNormMaxWidth = 1024;
 hipError_t launch_pgemm(const GemmArgs& a, AKind ak, EKind ek, bool norm, int parts, int cus, hipStream_t s);
 PgemmShapes pgemm_shapes(int N, int K, int parts, int cus, int max_rows);
 // Many-row projections of float32 models, the MLP router's hidden layer and

@@ -1,10 +1,12 @@
 // Per-row kernels: embedding + router, and RMSNorm of residual rows.
 //
 // Both keep the float32 residual row x and write y = RMSNorm(x) (no affine,
-// Appendix A), also float32: y is the A operand of the next projection
-// (QKV, gate/up, LM head), so the norm is computed once per row instead of
-// once per output tile.  Rows of up to 4096 elements stay in
-// registers between the sum of squares and the write of y.
+// Appendix A), the A operand of the next projection (QKV, gate/up, LM head), as
+// float32 or as bf16 operand rows of one or two parts, so that the norm is
+// computed once per row instead of once per output tile; where the projections
+// normalise, the embedding writes x itself as operand rows with its sum of
+// squares.  Rows of up to 4096 elements stay in registers between the sum of
+// squares and the write of y.
 #include "kernels.h"
 
 namespace tlf {
@@ -234,7 +236,8 @@ __global__ __launch_bounds__(256) void k_route_rows(RouteArgs a) {
 
 // ---------------------------------------------------------------------------
 // y[src(r)] = RMSNorm(x[src(r)]) for the active rows of a row map (prefill,
-// after each residual projection).  One wave per row, four rows per
+// after a residual projection that no normalising one follows), with an AdaLN
+// scale where the next operand has one.  One wave per row, four rows per
 // workgroup (most rows of the later loops are inactive, and a row's wave
 // leaves at once).  Lane l holds elements 4 (l + 64 v) + 1024 c, v < 4,
 // c < NC: those of threads l + 64 v of a 256-thread row.  Its sum of squares
